@@ -253,7 +253,7 @@ double pair_flops(const Resident& r, bool couple) {
 // at a time share few monomers' M and G blocks.
 void order_pairs(Resident* r) {
     const std::vector<MonoDesc>& m = r->monos;
-    auto lds = [&m](const PairDesc& d) { return pair_fits_lds(m[d.x].n, m[d.x].np, m[d.y].np); };
+    auto lds = [&m](const PairDesc& d) { return pair_fits_lds(m[d.x].n, m[d.y].n); };
     const int B = kPairBlock;
     std::stable_sort(r->pairs.begin(), r->pairs.end(), [&](const PairDesc& a, const PairDesc& b) {
         const bool la = lds(a), lb = lds(b);
@@ -341,7 +341,7 @@ mcpt_status upload_batch(mcpt_ctx* c, Exec& x, const mcpt_problem* pbs, int n_cl
             d.cluster = q;
             d.pad = 0;
             vo += (int64_t)r->monos[d.x].n * r->monos[d.y].n;
-            r->max_slot = std::max<int64_t>(r->max_slot, (int64_t)r->monos[d.x].np * r->monos[d.y].np);
+            r->max_slot = std::max(r->max_slot, pair_tau_slot(r->monos[d.x].n, r->monos[d.y].n));
         }
     }
     v_cl[n_cl] = vo;
@@ -2245,7 +2245,7 @@ mcpt_status join_concat(mcpt_ctx* c, Exec& x, const std::vector<std::pair<Reside
     M->raw_elems = raw;
     M->eps_elems = eps;
     for (const PairDesc& d : M->pairs)
-        M->max_slot = std::max<int64_t>(M->max_slot, (int64_t)M->monos[d.x].np * M->monos[d.y].np);
+        M->max_slot = std::max(M->max_slot, pair_tau_slot(M->monos[d.x].n, M->monos[d.y].n));
     order_pairs(M);
 #define ALLOC(ptr, n)                                          \
     do {                                                       \

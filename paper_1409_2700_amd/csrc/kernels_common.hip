@@ -171,13 +171,13 @@ __global__ __launch_bounds__(kMonoThreads) void monomer_kernel(
             Dx[e_rc] = tn;
             lo = 2.0 * tn - ts;
             has_lo = true;
-            if (Lt) Mx[e_rc] = lo;   // FP64 2 delta - S(delta) for the next intramonomer terms
+            if (Lt) Mx[frag_at(np, r, c)] = lo;   // FP64 2 delta - S(delta) for the next intramonomer terms
         } else if (mode == kMonoRlo) {
             tn = Rx[e_rc];
             ts = Rx[e_s];
             lo = 2.0 * tn - ts;
             has_lo = true;
-            if (Lt) Mx[e_rc] = lo;
+            if (Lt) Mx[frag_at(np, r, c)] = lo;
         } else if (mode == kMonoFromT) {
             tn = Tx[e_rc];
             ts = Tx[e_s];
@@ -189,7 +189,7 @@ __global__ __launch_bounds__(kMonoThreads) void monomer_kernel(
             const double m = 2.0 * tn - ts;
             esum += Kx[e_rc] * m;
             if (mode == kMonoInit || mode == kMonoUpdate || mode == kMonoUpdateR) Tx[e_rc] = tn;
-            if (mode != kMonoE0) Mx[e_rc] = m;
+            if (mode != kMonoE0) Mx[frag_at(np, r, c)] = m;
             if (!has_lo) {
                 lo = m;
                 has_lo = true;
@@ -311,8 +311,8 @@ __global__ __launch_bounds__(kMonoThreads) void monomer_blocks_kernel(
                     lo2 = 2.0 * t2 - t1;
                     has_lo = true;
                     if (Lt) {   // FP64 2 delta - S(delta) for the next intramonomer terms
-                        Mx[e1] = lo1;
-                        if (!diag) Mx[e2] = lo2;
+                        Mx[frag_at(np, r1, c1)] = lo1;
+                        if (!diag) Mx[frag_at(np, r2, c2)] = lo2;
                     }
                 } else if (mode == kMonoRlo) {
                     t1 = Rx[e1];
@@ -321,8 +321,8 @@ __global__ __launch_bounds__(kMonoThreads) void monomer_blocks_kernel(
                     lo2 = 2.0 * t2 - t1;
                     has_lo = true;
                     if (Lt) {
-                        Mx[e1] = lo1;
-                        if (!diag) Mx[e2] = lo2;
+                        Mx[frag_at(np, r1, c1)] = lo1;
+                        if (!diag) Mx[frag_at(np, r2, c2)] = lo2;
                     }
                 } else if (mode == kMonoFromT) {
                     t1 = Tx[e1];
@@ -340,8 +340,8 @@ __global__ __launch_bounds__(kMonoThreads) void monomer_blocks_kernel(
                         if (!diag) Tx[e2] = t2;
                     }
                     if (mode != kMonoE0) {
-                        Mx[e1] = m1;
-                        if (!diag) Mx[e2] = m2;
+                        Mx[frag_at(np, r1, c1)] = m1;
+                        if (!diag) Mx[frag_at(np, r2, c2)] = m2;
                     }
                     if (!has_lo) {
                         lo1 = m1;

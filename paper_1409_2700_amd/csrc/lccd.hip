@@ -148,11 +148,17 @@ __global__ __launch_bounds__(kLccdThreads, 2) void lccd_ring_kernel(
 #pragma unroll
             for (int u = 0; u < kRingSB; ++u) an[u] = load4(A + (int64_t)arow[u] * np + k0 + lk);
             if (kind == 0) {
-                const double* B = pr == 0 ? Mx : Tx;
+                if (pr == 0) {
 #pragma unroll
-                for (int w = 0; w < kRingSB; ++w)
+                    for (int w = 0; w < kRingSB; ++w)
 #pragma unroll
-                    for (int s = 0; s < 4; ++s) bn[w][s] = B[(int64_t)(k0 + lk + s) * np + bcol[w]];
+                        for (int s = 0; s < 4; ++s) bn[w][s] = Mx[frag_at(np, k0 + lk + s, bcol[w])];
+                } else {
+#pragma unroll
+                    for (int w = 0; w < kRingSB; ++w)
+#pragma unroll
+                        for (int s = 0; s < 4; ++s) bn[w][s] = Tx[(int64_t)(k0 + lk + s) * np + bcol[w]];
+                }
             } else {
 #pragma unroll
                 for (int w = 0; w < kRingSB; ++w)

@@ -4,7 +4,7 @@
 //   monomer X: o, v, n = o*v, np = n rounded up to 16; every per-monomer
 //   matrix (K, T, M, G) is np x np, row-major, row (i,a) = i*v + a, column
 //   (j,b) = j*v + b, zero in the padding; matrices of all monomers are
-//   concatenated at mat_off.
+//   concatenated at mat_off.  M is kept in fragment order (frag_at) instead of row-major.
 //   pair p = (X, Y): V_XY stored as given, nX x nY row-major (unpadded), at v_off.
 //   dif: per monomer np values d[(i,a)] = e_i - e_a (zero in the padding), so
 //   every denominator of Eqs. 60-61 is 1 / (d_X[(i,a)] + d_Y[(j,b)]).
@@ -23,6 +23,15 @@ constexpr int kMaxSweeps = 4096;       // length of the device residual history
 // (a closed-shell Coulomb loop; with it the equations are restricted LCCD,
 // Sec. II.A): the accumulated pair sums G and u enter the monomer updates twice.
 constexpr double kSpinSum = 2.0;
+
+// M = 2T - S(T) is read only as matrix-core operands, so it is stored in the order of their
+// fragments: 8 x 8 blocks of 64 values, block (r/8, c/8) at (r/8) (np/8) + c/8, inside a block
+// pairs of columns, then rows, then the column of the pair.  A fragment load (eight rows, one
+// column pair per 16-lane group) then covers whole cache lines; from row-major M each 16 bytes came
+// from another line and the L1 lookups, 70% busy, bounded the pair kernel.
+__host__ __device__ inline int64_t frag_at(int np, int r, int c) {
+    return ((int64_t)(r >> 3) * (np >> 3) + (c >> 3)) * 64 + ((c & 7) >> 1) * 16 + (r & 7) * 2 + (c & 1);
+}
 
 // 1 / d for the denominators of Eqs. 60-61 (negative, |d| well above zero):
 // the hardware reciprocal estimate refined by two Newton-Raphson steps
@@ -175,7 +184,10 @@ void launch_pair_fp64(int lds_variant, PartOut po, const PairDesc* pairs, int64_
                       double* scratch, int64_t slot_elems, int grid, double* ed2, int couple,
                       const Ctrl* ctrl, const ClState* cl, hipStream_t s);
 int pair_fp64_blocks_per_cu(int lds_variant);
-bool pair_fits_lds(int nX, int npX, int npY);
+bool pair_fits_lds(int nX, int nY);
+// doubles of a pair's Tau scratch slot: npX npY row-major, or (LDS variant) Tau and its transpose in
+// fragment order over nX and nY rounded up to 8
+int64_t pair_tau_slot(int nX, int nY);
 // Pairs read from L2 in two launches per chunk of at most one pair per persistent workgroup:
 // Tau of every pair (into the chunk's slots of the Tau scratch), then, if couple != 0, G.  Pair k
 // of a chunk belongs to XCD k % 8, whose workgroups take its pairs' tasks (3 x 3 tile blocks) in
