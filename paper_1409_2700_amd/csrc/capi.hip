@@ -314,6 +314,7 @@ mcpt_status upload_batch(mcpt_ctx* c, Exec& x, const mcpt_problem* pbs, int n_cl
             roff += (int64_t)d.n * d.n;
             moff += (int64_t)d.np * d.np;
             r->max_n = std::max(r->max_n, d.n);
+            r->max_o = std::max(r->max_o, d.o);
             r->max_v = std::max(r->max_v, d.v);
             r->max_np = std::max(r->max_np, d.np);
         }
@@ -883,7 +884,7 @@ void mixed_mono(mcpt_ctx* c, Exec& x, Resident* R, int mode, const double* G, do
                 const float* Gf = nullptr, float* Gfz = nullptr) {
     // full monomer equation: the update and correction modes add the intramonomer terms held in L
     const bool with_l = R->lccd && (mode == kMonoUpdate || mode == kMonoUpdateR || mode == kMonoCorr || mode == kMonoRlo);
-    launch_monomer_mixed(mode, R->lo_prec, R->d_monos, R->n_mono, R->max_v, R->d_dif, R->d_K, G, Gz, R->d_T, R->d_M, R->d_R,
+    launch_monomer_mixed(mode, R->lo_prec, R->d_monos, R->n_mono, R->max_o, R->max_v, R->d_dif, R->d_K, G, Gz, R->d_T, R->d_M, R->d_R,
                          R->d_Dl, lo_out ? R->d_Mlo : nullptr, R->d_mlo_off, R->d_em2, R->d_em2_0, R->d_res, ctrl,
                          R->d_cl, x.stream, Gf, Gfz, with_l ? R->d_L : nullptr);
 }
@@ -1498,6 +1499,7 @@ mcpt_status clone_scaled(mcpt_ctx* c, Exec& x, Resident* B, int64_t n, const int
     R->n_pair = B->n_pair;
     R->max_n = B->max_n;
     R->max_np = B->max_np;
+    R->max_o = B->max_o;
     R->max_v = B->max_v;
     R->eps_elems = B->eps_elems;
     R->dif_elems = B->dif_elems;
@@ -1740,7 +1742,7 @@ mcpt_status run(mcpt_ctx* c, Exec& x, Resident* R, const mcpt_options* o, mcpt_s
     if (R->lccd) {
         // step 5: every monomer's LCCD without its environment (no pair phase, G stays zero),
         // same stopping rule; E_LCCD(X) is kept as the reference of Eq. 56
-        launch_monomer(kMonoInit, R->d_monos, R->n_mono, R->max_v, R->d_dif, R->d_K, nullptr, nullptr, R->d_T, R->d_M,
+        launch_monomer(kMonoInit, R->d_monos, R->n_mono, R->max_o, R->max_v, R->d_dif, R->d_K, nullptr, nullptr, R->d_T, R->d_M,
                        R->d_em2, R->d_em2_0, R->d_res, nullptr, nullptr, s);
         const int every5 = o->check_every > 0 ? o->check_every : 1;
         int issued = 0;
@@ -1748,7 +1750,7 @@ mcpt_status run(mcpt_ctx* c, Exec& x, Resident* R, const mcpt_options* o, mcpt_s
             const int batch = std::min(every5, o->max_sweeps - issued);
             for (int k = 0; k < batch; ++k) {
                 lccd_terms(x.d_ctrl);
-                launch_monomer(kMonoUpdate, R->d_monos, R->n_mono, R->max_v, R->d_dif, R->d_K, R->d_G[0], R->d_G[1],
+                launch_monomer(kMonoUpdate, R->d_monos, R->n_mono, R->max_o, R->max_v, R->d_dif, R->d_K, R->d_G[0], R->d_G[1],
                                R->d_T, R->d_M, R->d_em2, R->d_em2_0, R->d_res, x.d_ctrl, R->d_cl, s, R->d_L);
                 launch_reduce_sweep(R->n_cl, R->d_cl_mono, R->d_res, R->d_cl, R->d_hist, x.d_ctrl, s);
                 ++issued;
@@ -1757,6 +1759,7 @@ mcpt_status run(mcpt_ctx* c, Exec& x, Resident* R, const mcpt_options* o, mcpt_s
             if (h.done) break;
         }
         std::vector<ClState> cs(R->n_cl);
+        launch_energy(R->d_monos, R->n_mono, R->d_K, R->d_M, R->d_em2, nullptr, nullptr, s);
         HIP_TRY(hipMemcpyAsync(cs.data(), R->d_cl, R->n_cl * sizeof(ClState), hipMemcpyDeviceToHost, s));
         HIP_TRY(hipMemcpyAsync(R->d_elccd, R->d_em2, R->n_mono * sizeof(double), hipMemcpyDeviceToDevice, s));
         HIP_TRY(hipStreamSynchronize(s));
@@ -1779,13 +1782,15 @@ mcpt_status run(mcpt_ctx* c, Exec& x, Resident* R, const mcpt_options* o, mcpt_s
         HIP_TRY(hipMemcpyAsync(R->d_raw, o->warm_t, R->raw_elems * sizeof(double), hipMemcpyHostToDevice, s));
         launch_fill(R->d_T, R->mat_elems, 0.0, s);
         launch_pack(R->d_monos, R->n_mono, R->d_raw, R->d_T, R->max_n, s);
-        launch_monomer(kMonoE0, R->d_monos, R->n_mono, R->max_v, R->d_dif, R->d_K, nullptr, nullptr, R->d_T, R->d_M,
+        launch_monomer(kMonoE0, R->d_monos, R->n_mono, R->max_o, R->max_v, R->d_dif, R->d_K, nullptr, nullptr, R->d_T, R->d_M,
                        R->d_em2, R->d_em2_0, R->d_res, nullptr, nullptr, s);
-        launch_monomer(kMonoFromT, R->d_monos, R->n_mono, R->max_v, R->d_dif, R->d_K, nullptr, nullptr, R->d_T,
+        launch_monomer(kMonoFromT, R->d_monos, R->n_mono, R->max_o, R->max_v, R->d_dif, R->d_K, nullptr, nullptr, R->d_T,
                        R->d_M, R->d_em2, R->d_em2_0, R->d_res, nullptr, nullptr, s);
     } else {
-        launch_monomer(kMonoInit, R->d_monos, R->n_mono, R->max_v, R->d_dif, R->d_K, nullptr, nullptr, R->d_T, R->d_M,
+        launch_monomer(kMonoInit, R->d_monos, R->n_mono, R->max_o, R->max_v, R->d_dif, R->d_K, nullptr, nullptr, R->d_T, R->d_M,
                        R->d_em2, R->d_em2_0, R->d_res, nullptr, nullptr, s);
+        if (!R->lccd)   // E_M2 at zero coupling
+            launch_energy(R->d_monos, R->n_mono, R->d_K, R->d_M, R->d_em2, R->d_em2_0, nullptr, s);
     }
     if (prec != MCPT_FP64) mixed_mono(c, x, R, kMonoFromT, nullptr, nullptr, true, nullptr);   // M in low precision
     HIP_TRY(hipGetLastError());
@@ -1823,7 +1828,7 @@ mcpt_status run(mcpt_ctx* c, Exec& x, Resident* R, const mcpt_options* o, mcpt_s
             if (prec == MCPT_FP64) {
                 pair_phase(c, x, R, R->d_G[cur], 1, x.d_ctrl);
                 if (R->lccd) lccd_terms(x.d_ctrl);
-                launch_monomer(kMonoUpdate, R->d_monos, R->n_mono, R->max_v, R->d_dif, R->d_K, R->d_G[cur], R->d_G[cur ^ 1],
+                launch_monomer(kMonoUpdate, R->d_monos, R->n_mono, R->max_o, R->max_v, R->d_dif, R->d_K, R->d_G[cur], R->d_G[cur ^ 1],
                                R->d_T, R->d_M, R->d_em2, R->d_em2_0, R->d_res, x.d_ctrl, R->d_cl, s,
                                R->lccd ? R->d_L : nullptr);
                 cur ^= 1;
@@ -1882,7 +1887,7 @@ mcpt_status run(mcpt_ctx* c, Exec& x, Resident* R, const mcpt_options* o, mcpt_s
                 }
                 record_begin(x, &a);
                 if (prec == MCPT_FP64) {
-                    launch_monomer(kMonoUpdate, R->d_monos, R->n_mono, R->max_v, R->d_dif, R->d_K, R->d_G[cur],
+                    launch_monomer(kMonoUpdate, R->d_monos, R->n_mono, R->max_o, R->max_v, R->d_dif, R->d_K, R->d_G[cur],
                                    R->d_G[cur ^ 1], R->d_T, R->d_M, R->d_em2, R->d_em2_0, R->d_res, x.d_ctrl,
                                    R->d_cl, s, R->lccd ? R->d_L : nullptr);
                     cur ^= 1;
@@ -1931,6 +1936,7 @@ mcpt_status run(mcpt_ctx* c, Exec& x, Resident* R, const mcpt_options* o, mcpt_s
             record_end(x, a, 2, fl_sweep, R->lo_v_bytes);
             lo_mono(kMonoUpdate, nullptr);
         }
+        launch_fill(R->d_res, R->n_mono, 0.0, s);   // those sweeps' residuals are nobody's
         fp64_sweep();
         if ((st = sync_ctrl(x)) != MCPT_OK) return st;
         if (o->graph && !h.done) {
@@ -2005,6 +2011,7 @@ mcpt_status run(mcpt_ctx* c, Exec& x, Resident* R, const mcpt_options* o, mcpt_s
     }
     if (R->lccd)   // the reference of Eq. 56 is the isolated-monomer LCCD energy of step 5
         HIP_TRY(hipMemcpyAsync(R->d_em2_0, R->d_elccd, R->n_mono * sizeof(double), hipMemcpyDeviceToDevice, s));
+    launch_energy(R->d_monos, R->n_mono, R->d_K, R->d_M, R->d_em2, nullptr, nullptr, s);
     launch_reduce_final(R->n_cl, R->d_cl_mono, R->d_cl_pair, R->d_em2, R->d_em2_0, R->d_ed2, R->d_cl, x.d_ctrl, s);
     if ((st = sync_ctrl(x)) != MCPT_OK) return st;
     if (x.timing.on) drain_timing(x.timing);
@@ -2073,8 +2080,9 @@ mcpt_status join_init(mcpt_ctx* c, Exec& x, Resident* R) {
             cs[q].status = MCPT_ERR_NONFINITE;
         }
     HIP_TRY(hipMemcpyAsync(R->d_cl, cs.data(), R->n_cl * sizeof(ClState), hipMemcpyHostToDevice, s));
-    launch_monomer(kMonoInit, R->d_monos, R->n_mono, R->max_v, R->d_dif, R->d_K, nullptr, nullptr, R->d_T, R->d_M,
+    launch_monomer(kMonoInit, R->d_monos, R->n_mono, R->max_o, R->max_v, R->d_dif, R->d_K, nullptr, nullptr, R->d_T, R->d_M,
                    R->d_em2, R->d_em2_0, R->d_res, nullptr, nullptr, s);
+    launch_energy(R->d_monos, R->n_mono, R->d_K, R->d_M, R->d_em2, R->d_em2_0, nullptr, s);
     HIP_TRY(hipGetLastError());
     HIP_TRY(hipStreamSynchronize(s));
     R->g_cur = 0;   // upload left both G buffers zero
@@ -2096,7 +2104,7 @@ mcpt_status join_sweeps(mcpt_ctx* c, Exec& x, Resident* R, const mcpt_options* o
     for (int k = 0; k < every; ++k) {
         int& cur = R->g_cur;
         pair_phase(c, x, R, R->d_G[cur], 1, x.d_ctrl);
-        launch_monomer(kMonoUpdate, R->d_monos, R->n_mono, R->max_v, R->d_dif, R->d_K, R->d_G[cur], R->d_G[cur ^ 1],
+        launch_monomer(kMonoUpdate, R->d_monos, R->n_mono, R->max_o, R->max_v, R->d_dif, R->d_K, R->d_G[cur], R->d_G[cur ^ 1],
                        R->d_T, R->d_M, R->d_em2, R->d_em2_0, R->d_res, x.d_ctrl, R->d_cl, s);
         cur ^= 1;
         launch_reduce_sweep(R->n_cl, R->d_cl_mono, R->d_res, R->d_cl, R->d_hist, x.d_ctrl, s);
@@ -2130,6 +2138,7 @@ mcpt_status join_finish(mcpt_ctx* c, Exec& x, Resident* R, const std::vector<int
         for (int q = 0; q < R->n_cl; ++q) sel[q].done = keep[q] ? 0 : 1;
         HIP_TRY(hipMemcpyAsync(R->d_cl_sel, sel.data(), R->n_cl * sizeof(ClState), hipMemcpyHostToDevice, s));
         pair_phase(c, x, R, R->d_G[R->g_cur], 0, nullptr, R->d_cl_sel);
+        launch_energy(R->d_monos, R->n_mono, R->d_K, R->d_M, R->d_em2, nullptr, R->d_cl_sel, s);
         launch_reduce_final(R->n_cl, R->d_cl_mono, R->d_cl_pair, R->d_em2, R->d_em2_0, R->d_ed2, R->d_cl, x.d_ctrl, s);
         HIP_TRY(hipGetLastError());
         HIP_TRY(hipMemcpyAsync(cs.data(), R->d_cl, R->n_cl * sizeof(ClState), hipMemcpyDeviceToHost, s));
@@ -2214,6 +2223,7 @@ mcpt_status join_concat(mcpt_ctx* c, Exec& x, const std::vector<std::pair<Reside
             d.cluster = k;
             M->monos.push_back(d);
             M->max_n = std::max(M->max_n, d.n);
+            M->max_o = std::max(M->max_o, d.o);
             M->max_v = std::max(M->max_v, d.v);
             M->max_np = std::max(M->max_np, d.np);
         }

@@ -1,6 +1,7 @@
 // Elementwise and reduction kernels of the MCPT(2) path: layout packing, the
 // monomer phase (Eq. 58 divided by its denominators, Eq. 54 energy) and the
 // per-sweep residual / stopping rule.
+#include <algorithm>
 #include <cfloat>
 #include <cmath>
 
@@ -12,6 +13,7 @@ namespace {
 
 constexpr int kMonoThreads = 256;
 constexpr int kReduceThreads = 1024;
+constexpr int kMonoGroups = 4096;   // workgroups of the monomer phase, at most
 
 __global__ void fill_kernel(double* __restrict__ p, int64_t n, double value) {
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
@@ -91,7 +93,7 @@ __device__ double block_max(double x, double* sh) {
 // spin-adapted combination 2X - S(X) of Eq. 59 needs no second pass (values at
 // S(r, c) are recomputed from inputs, never read from an output).
 // E_M2 = <2K - S(K), T> = <K, M> (Eq. 54).  Modes:
-//   init      T = D K, M, E_M2 -> em2 and em2_0
+//   init      T = D K, M, E_M2 -> em2 and em2_0 (energies: this element-wise kernel; see energy_kernel)
 //   update    T' = D (K + 2 (G + G^T)), residual |T' - T|, M', E_M2(T')  (2: spin sum)
 //   from_t    M and E_M2 of the stored T
 //   e0        E_M2 of D K into em2_0 only
@@ -211,7 +213,7 @@ __global__ __launch_bounds__(kMonoThreads) void monomer_kernel(
         } else {
             em2[x] = etot;
             if (mode == kMonoInit) em2_0[x] = etot;
-            if (mode == kMonoUpdate || mode == kMonoUpdateR) res[x] = rtot;
+            res[x] = mode == kMonoUpdate || mode == kMonoUpdateR ? rtot : 0.0;
         }
     }
 }
@@ -224,20 +226,27 @@ __global__ __launch_bounds__(kMonoThreads) void monomer_kernel(
 // ((a,b) -> (a,b)), and G^T at (i,a),(j,b) is element (b,a) of block (j,i).  One
 // pass over the block pair {(i,j), (j,i)} therefore reads every element once:
 // K, T and R along contiguous block rows, G through LDS for the transposed
-// read.  Results are bitwise those of monomer_kernel (same operations in the
+// read.  The amplitudes are bitwise those of monomer_kernel (same operations in the
 // same order per element).
+//
+// The o (o + 1) / 2 block pairs of a monomer are dealt out to `splits` workgroups.  What bounds it is
+// HBM for many monomers and latency for few: with one workgroup per monomer an update took 100 us for
+// 8 monomers of o5v27, 140 for 125, 310 for 1000, and 1230 us for 120 of o5v27 and o8v56 (36 dependent rounds
+// of 56 x 56 blocks); dealt out it takes 13, 43, 291 (3.0 TB/s) and 318 us.  Since no workgroup sees a whole monomer, the
+// residual is a maximum over the monomer in memory (reduce_sweep_kernel takes it and clears it) and the energy
+// is left to energy_kernel; the e0 mode, which only forms an energy, keeps one workgroup per monomer.
 template <class E, int VMAX, class GT>
 __global__ __launch_bounds__(kMonoThreads) void monomer_blocks_kernel(
-    int mode, const MonoDesc* __restrict__ monos, const double* __restrict__ dif,
+    int mode, int splits, const MonoDesc* __restrict__ monos, const double* __restrict__ dif,
     const double* __restrict__ K, const GT* __restrict__ G, GT* __restrict__ Gz,
     double* __restrict__ T, double* __restrict__ M, double* __restrict__ R, double* __restrict__ Dl,
-    E* __restrict__ Mlo, const int64_t* __restrict__ mlo_off, int lo_chunk, double* __restrict__ em2,
-    double* __restrict__ em2_0, double* __restrict__ res, const Ctrl* __restrict__ ctrl,
+    E* __restrict__ Mlo, const int64_t* __restrict__ mlo_off, int lo_chunk, double* __restrict__ em2_0,
+    double* __restrict__ res, const Ctrl* __restrict__ ctrl,
     const ClState* __restrict__ cl, const double* __restrict__ Lt) {
     if (ctrl && ctrl->done) return;
     __shared__ double sh[kMonoThreads];
     __shared__ double sg[2][VMAX][VMAX + 1];
-    const int x = blockIdx.x;
+    const int x = blockIdx.x / splits, part = blockIdx.x - x * splits;
     const MonoDesc d = monos[x];
     if (cl && cl[d.cluster].done) return;   // this monomer's cluster has stopped
     const int o = d.o, v = d.v, n = d.n, np = d.np;
@@ -252,8 +261,11 @@ __global__ __launch_bounds__(kMonoThreads) void monomer_blocks_kernel(
     const int ldl = (n + lo_chunk - 1) / lo_chunk * lo_chunk;
     const bool need_g = mode == kMonoUpdate || mode == kMonoUpdateR || mode == kMonoCorr;
     double rmax = 0.0, esum = 0.0;
-    for (int i = 0; i < o; ++i)
-        for (int j = i; j < o; ++j) {
+    const int n_bp = o * (o + 1) / 2;
+    for (int bp = part; bp < n_bp; bp += splits) {
+            int i = 0, j = bp;   // row i of the triangle holds the pairs (i, i) .. (i, o - 1)
+            while (j >= o - i) j -= o - i++;
+            j += i;
             const bool diag = i == j;
             if (need_g) {
                 __syncthreads();   // the previous block pair is done with sg
@@ -333,8 +345,10 @@ __global__ __launch_bounds__(kMonoThreads) void monomer_blocks_kernel(
                 }
                 if (mode != kMonoCorr && mode != kMonoRlo) {
                     const double m1 = 2.0 * t1 - t2, m2 = 2.0 * t2 - t1;
-                    esum += Kx[e1] * m1;
-                    if (!diag) esum += Kx[e2] * m2;
+                    if (mode == kMonoE0) {
+                        esum += Kx[e1] * m1;
+                        if (!diag) esum += Kx[e2] * m2;
+                    }
                     if (mode == kMonoInit || mode == kMonoUpdate || mode == kMonoUpdateR) {
                         Tx[e1] = t1;
                         if (!diag) Tx[e2] = t2;
@@ -353,38 +367,65 @@ __global__ __launch_bounds__(kMonoThreads) void monomer_blocks_kernel(
                     Ml[(int64_t)r1 * ldl + c1] = (E)(float)lo1;
                     if (!diag) Ml[(int64_t)r2 * ldl + c2] = (E)(float)lo2;
                 }
+                if (Gz) {   // the padding is never added to
+                    Gz[d.mat_off + e1] = GT(0);
+                    Gz[d.mat_off + e2] = GT(0);
+                }
             }
         }
-    if (Gz) {
-        GT* gz = Gz + d.mat_off;
-        const int npp = np * np;
-        for (int idx = threadIdx.x; idx < npp; idx += kMonoThreads) gz[idx] = GT(0);
+    if (mode == kMonoE0) {   // one workgroup per monomer
+        const double etot = block_sum<kMonoThreads>(esum, sh);
+        if (threadIdx.x == 0) em2_0[x] = etot;
+    } else if (mode == kMonoInit || mode == kMonoFromT) {
+        if (part == 0 && threadIdx.x == 0) res[x] = 0.0;
+    } else if (mode == kMonoUpdate || mode == kMonoUpdateR) {
+        const double rtot = block_max<kMonoThreads>(rmax, sh);
+        // non-negative or NaN: ordered as integers, NaN last
+        if (threadIdx.x == 0)
+            atomicMax(reinterpret_cast<unsigned long long*>(res + x),
+                      __builtin_bit_cast(unsigned long long, fabs(rtot)));
     }
-    if (mode == kMonoApply || mode == kMonoRlo || mode == kMonoCorr) return;
-    const double etot = block_sum<kMonoThreads>(esum, sh);
-    const double rtot = block_max<kMonoThreads>(rmax, sh);
+}
+
+// E_M2(X) = <K, M> (Eq. 54) of the stored M, one workgroup per monomer, into em2 and (not null) em2_0
+__global__ __launch_bounds__(kReduceThreads) void energy_kernel(const MonoDesc* __restrict__ monos,
+                                                                const double* __restrict__ K,
+                                                                const double* __restrict__ M, double* __restrict__ em2,
+                                                                double* __restrict__ em2_0,
+                                                                const ClState* __restrict__ cl) {
+    const MonoDesc d = monos[blockIdx.x];
+    if (cl && cl[d.cluster].done) return;
+    __shared__ double sh[kReduceThreads];
+    const int n = d.n, np = d.np;
+    double e = 0.0;
+    // threads walk M in its own (fragment) order: pairs of columns, eight rows
+    for (int64_t idx = threadIdx.x; idx < (int64_t)np * np; idx += kReduceThreads) {
+        const int blk = (int)(idx >> 6), in = (int)(idx & 63), nb = np >> 3;
+        const int r = (blk / nb) * 8 + ((in & 15) >> 1), c = (blk % nb) * 8 + (in >> 4) * 2 + (in & 1);
+        if (r < n && c < n) e += K[d.mat_off + (int64_t)r * np + c] * M[d.mat_off + idx];
+    }
+    e = block_sum<kReduceThreads>(e, sh);
     if (threadIdx.x == 0) {
-        if (mode == kMonoE0) {
-            em2_0[x] = etot;
-        } else {
-            em2[x] = etot;
-            if (mode == kMonoInit) em2_0[x] = etot;
-            if (mode == kMonoUpdate || mode == kMonoUpdateR) res[x] = rtot;
-        }
+        em2[blockIdx.x] = e;
+        if (em2_0) em2_0[blockIdx.x] = e;
     }
 }
 
 // Convergence test of one sweep, one workgroup per cluster: max|dT| over the
-// cluster's monomers, its residual history and the stopping rules (tolerance,
-// divergence, sweep limit).  Clusters that have stopped are left untouched.
+// cluster's monomers (cleared for the next sweep), its residual history and the stopping rules (tolerance,
+// divergence, sweep limit).  Clusters that have stopped are left untouched.  One cluster's
+// state is the batch's (reduce_ctrl_kernel has nothing to add: one launch less per sweep).
 __global__ __launch_bounds__(kReduceThreads) void reduce_sweep_kernel(
-    const int64_t* __restrict__ cl_mono, const double* __restrict__ res, ClState* __restrict__ cl,
-    double* __restrict__ hist_all, const Ctrl* __restrict__ ctrl) {
+    const int64_t* __restrict__ cl_mono, double* __restrict__ res, ClState* __restrict__ cl,
+    double* __restrict__ hist_all, Ctrl* __restrict__ ctrl) {
     const int q = blockIdx.x;
     if (ctrl->done || cl[q].done) return;
     __shared__ double sh[kReduceThreads];
     double m = 0.0;
-    for (int64_t i = cl_mono[q] + threadIdx.x; i < cl_mono[q + 1]; i += kReduceThreads) m = max_nan(m, res[i]);
+    for (int64_t i = cl_mono[q] + threadIdx.x; i < cl_mono[q + 1]; i += kReduceThreads) {
+        m = max_nan(m, res[i]);
+        res[i] = 0.0;
+    }
     const double r = block_max<kReduceThreads>(m, sh);
     if (threadIdx.x != 0) return;
     double* h = hist_all + (int64_t)q * kMaxSweeps;
@@ -412,6 +453,12 @@ __global__ __launch_bounds__(kReduceThreads) void reduce_sweep_kernel(
     cl[q].residual = r;
     cl[q].status = status;
     cl[q].done = done;
+    if (gridDim.x == 1) {
+        ctrl->sweeps = s + 1;
+        ctrl->residual = r;
+        ctrl->status = status;
+        ctrl->done = done;
+    }
 }
 
 // Batch-wide view of the per-cluster states: done when every cluster is, the
@@ -536,50 +583,62 @@ void launch_nonfinite(const double* p, int64_t n, int32_t* flag, hipStream_t s) 
 
 // Blocked kernel when every monomer's v fits its LDS tiles, the element-wise one otherwise.
 template <class E, class GT>
-void monomer_dispatch(int max_v, int mode, const MonoDesc* monos, int n_mono, const double* dif, const double* K,
+void monomer_dispatch(int max_o, int max_v, int mode, const MonoDesc* monos, int n_mono, const double* dif, const double* K,
                       const GT* G, GT* G_zero, double* T, double* M, double* R, double* Dl, E* Mlo,
                       const int64_t* mlo_off, int chunk, double* em2, double* em2_0, double* res, const Ctrl* ctrl,
                       const ClState* cl, hipStream_t s, const double* Lt = nullptr) {
     if (n_mono <= 0) return;
+    // Workgroups per monomer: about four per compute unit of the chip in all, at most one per block pair of
+    // the largest monomer (15 for o = 5; a workgroup without one ends at once).  Measured with o5v27: see the kernel.
+    const int pairs = max_o * (max_o + 1) / 2;
+    const int splits = mode == kMonoE0 ? 1 : std::max(1, std::min(pairs, kMonoGroups / n_mono));
     if (max_v <= 32)
-        hipLaunchKernelGGL((monomer_blocks_kernel<E, 32, GT>), dim3(n_mono), dim3(kMonoThreads), 0, s, mode, monos,
-                           dif, K, G, G_zero, T, M, R, Dl, Mlo, mlo_off, chunk, em2, em2_0, res, ctrl, cl, Lt);
+        hipLaunchKernelGGL((monomer_blocks_kernel<E, 32, GT>), dim3((unsigned)n_mono * splits), dim3(kMonoThreads), 0, s,
+                           mode, splits, monos, dif, K, G, G_zero, T, M, R, Dl, Mlo, mlo_off, chunk, em2_0, res, ctrl, cl,
+                           Lt);
     else if (max_v <= 64)
-        hipLaunchKernelGGL((monomer_blocks_kernel<E, 64, GT>), dim3(n_mono), dim3(kMonoThreads), 0, s, mode, monos,
-                           dif, K, G, G_zero, T, M, R, Dl, Mlo, mlo_off, chunk, em2, em2_0, res, ctrl, cl, Lt);
+        hipLaunchKernelGGL((monomer_blocks_kernel<E, 64, GT>), dim3((unsigned)n_mono * splits), dim3(kMonoThreads), 0, s,
+                           mode, splits, monos, dif, K, G, G_zero, T, M, R, Dl, Mlo, mlo_off, chunk, em2_0, res, ctrl, cl,
+                           Lt);
     else
         hipLaunchKernelGGL((monomer_kernel<E, GT>), dim3(n_mono), dim3(kMonoThreads), 0, s, mode, monos, dif, K, G,
                            G_zero, T, M, R, Dl, Mlo, mlo_off, chunk, em2, em2_0, res, ctrl, cl, Lt);
 }
 
-void launch_monomer(int mode, const MonoDesc* monos, int n_mono, int max_v, const double* dif, const double* K,
+void launch_monomer(int mode, const MonoDesc* monos, int n_mono, int max_o, int max_v, const double* dif, const double* K,
                     const double* G, double* G_zero, double* T, double* M, double* em2,
                     double* em2_0, double* res, const Ctrl* ctrl, const ClState* cl, hipStream_t s,
                     const double* L) {
-    monomer_dispatch<float, double>(max_v, mode, monos, n_mono, dif, K, G, G_zero, T, M, nullptr, nullptr, nullptr,
+    monomer_dispatch<float, double>(max_o, max_v, mode, monos, n_mono, dif, K, G, G_zero, T, M, nullptr, nullptr, nullptr,
                                     nullptr, 16, em2, em2_0, res, ctrl, cl, s, L);
 }
 
-void launch_monomer_mixed(int mode, int precision, const MonoDesc* monos, int n_mono, int max_v, const double* dif,
+void launch_monomer_mixed(int mode, int precision, const MonoDesc* monos, int n_mono, int max_o, int max_v, const double* dif,
                           const double* K, const double* G, double* G_zero, double* T, double* M, double* R,
                           double* Dl, void* Mlo, const int64_t* mlo_off, double* em2, double* em2_0,
                           double* res, const Ctrl* ctrl, const ClState* cl, hipStream_t s, const float* Gf,
                           float* Gf_zero, const double* L) {
     if (precision == 2 && (Gf || Gf_zero))
-        monomer_dispatch<__bf16, float>(max_v, mode, monos, n_mono, dif, K, Gf, Gf_zero, T, M, R, Dl,
+        monomer_dispatch<__bf16, float>(max_o, max_v, mode, monos, n_mono, dif, K, Gf, Gf_zero, T, M, R, Dl,
                                         static_cast<__bf16*>(Mlo), mlo_off, 32, em2, em2_0, res, ctrl, cl, s, L);
     else if (precision == 2)
-        monomer_dispatch<__bf16, double>(max_v, mode, monos, n_mono, dif, K, G, G_zero, T, M, R, Dl,
+        monomer_dispatch<__bf16, double>(max_o, max_v, mode, monos, n_mono, dif, K, G, G_zero, T, M, R, Dl,
                                          static_cast<__bf16*>(Mlo), mlo_off, 32, em2, em2_0, res, ctrl, cl, s, L);
     else
-        monomer_dispatch<float, double>(max_v, mode, monos, n_mono, dif, K, G, G_zero, T, M, R, Dl,
+        monomer_dispatch<float, double>(max_o, max_v, mode, monos, n_mono, dif, K, G, G_zero, T, M, R, Dl,
                                         static_cast<float*>(Mlo), mlo_off, 16, em2, em2_0, res, ctrl, cl, s, L);
 }
 
-void launch_reduce_sweep(int n_cl, const int64_t* cl_mono, const double* res, ClState* cl, double* hist,
+void launch_reduce_sweep(int n_cl, const int64_t* cl_mono, double* res, ClState* cl, double* hist,
                          Ctrl* ctrl, hipStream_t s) {
     hipLaunchKernelGGL(reduce_sweep_kernel, dim3(n_cl), dim3(kReduceThreads), 0, s, cl_mono, res, cl, hist, ctrl);
-    hipLaunchKernelGGL(reduce_ctrl_kernel, dim3(1), dim3(kReduceThreads), 0, s, n_cl, cl, ctrl);
+    if (n_cl > 1) hipLaunchKernelGGL(reduce_ctrl_kernel, dim3(1), dim3(kReduceThreads), 0, s, n_cl, cl, ctrl);
+}
+
+void launch_energy(const MonoDesc* monos, int n_mono, const double* K, const double* M, double* em2, double* em2_0,
+                   const ClState* cl, hipStream_t s) {
+    if (n_mono <= 0) return;
+    hipLaunchKernelGGL(energy_kernel, dim3(n_mono), dim3(kReduceThreads), 0, s, monos, K, M, em2, em2_0, cl);
 }
 
 void launch_reduce_parts(const MonoDesc* monos, int n_mono, const int64_t* csr_off, const int64_t* csr,

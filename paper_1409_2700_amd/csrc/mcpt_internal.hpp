@@ -133,9 +133,9 @@ struct Ctrl {
 };
 
 enum MonoMode : int {
-    kMonoInit = 0,      // T = D*K, M, E_M2 -> em2 and em2_0
+    kMonoInit = 0,      // T = D*K, M
     kMonoUpdate = 1,    // T' = D*(K + G + G^T), residual, M', E_M2(T')
-    kMonoFromT = 2,     // M and E_M2 from the T already stored
+    kMonoFromT = 2,     // M from the T already stored
     kMonoE0 = 3,        // E_M2 of D*K into em2_0 only (warm starts)
     kMonoUpdateR = 4,   // update, keeping R = T' - T (FP64 polish sweep)
     kMonoCorr = 5,      // delta = R + D*(G + G^T), low-precision 2 delta - S(delta)
@@ -153,19 +153,24 @@ void launch_nonfinite(const double* p, int64_t n, int32_t* flag, hipStream_t s);
 // V[off[b] .. off[b] + len[b]) *= f[b] for b < n
 void launch_scale_blocks(const int64_t* off, const int64_t* len, const double* f, int64_t n, double* V,
                          hipStream_t s);
-void launch_monomer(int mode, const MonoDesc* monos, int n_mono, int max_v, const double* dif,
+// Monomer phase.  Forms no energy except in mode e0 (launch_energy does, from the stored M) but for
+// monomers with v > 64; the update modes leave max|T' - T| in res, which launch_reduce_sweep clears.
+void launch_monomer(int mode, const MonoDesc* monos, int n_mono, int max_o, int max_v, const double* dif,
                     const double* K, const double* G, double* G_zero, double* T, double* M,
                     double* em2, double* em2_0, double* res, const Ctrl* ctrl, const ClState* cl,
                     hipStream_t s, const double* L = nullptr);   // L: extra term of the update (full monomer equation)
 // Gf / Gf_zero: the FP32 accumulation buffers of BF16 sweeps, read and cleared instead of G / G_zero
-void launch_monomer_mixed(int mode, int precision, const MonoDesc* monos, int n_mono, int max_v, const double* dif,
+void launch_monomer_mixed(int mode, int precision, const MonoDesc* monos, int n_mono, int max_o, int max_v, const double* dif,
                           const double* K, const double* G, double* G_zero, double* T, double* M, double* R,
                           double* Dl, void* Mlo, const int64_t* mlo_off, double* em2, double* em2_0,
                           double* res, const Ctrl* ctrl, const ClState* cl, hipStream_t s,
                           const float* Gf = nullptr, float* Gf_zero = nullptr, const double* L = nullptr);
 // (L: the intramonomer terms of the full monomer equation, added by the update and correction modes;
 //  with L, the rlo and corr modes also store the FP64 2 delta - S(delta) in M)
-void launch_reduce_sweep(int n_cl, const int64_t* cl_mono, const double* res, ClState* cl, double* hist,
+// E_M2 = <K, M> of every monomer (of clusters not done, if cl) into em2 and, not null, em2_0
+void launch_energy(const MonoDesc* monos, int n_mono, const double* K, const double* M, double* em2, double* em2_0,
+                   const ClState* cl, hipStream_t s);
+void launch_reduce_sweep(int n_cl, const int64_t* cl_mono, double* res, ClState* cl, double* hist,
                          Ctrl* ctrl, hipStream_t s);
 // G_X = sum of the stored partial blocks of monomer X (csr[csr_off[X] .. csr_off[X+1]):
 // offsets into part, in pair order); skips stopped clusters
