@@ -702,7 +702,7 @@ void pair_phase(mcpt_ctx* c, Exec& x, Resident* R, double* G, int couple, const 
         launch_pair_fp64(0, p1, R->d_pairs + R->n_lds, R->n_pair - R->n_lds, R->d_monos, R->d_dif, R->d_V, R->d_M,
                          G, x.d_scratch, x.scratch_slot, g_glb, R->d_ed2, couple, ctrl, cl, x.stream);
     }
-    if (det) launch_reduce_parts(R->d_monos, R->n_mono, R->d_csr_off, R->d_csr, R->d_part, G, R->d_cl, ctrl, x.stream);
+    if (det) launch_reduce_parts(R->d_monos, R->n_mono, R->max_np, R->d_csr_off, R->d_csr, R->d_part, G, R->d_cl, ctrl, x.stream);
 }
 
 // Buffers of the deterministic mode: a partial G_X and G_Y block per pair and,
@@ -877,7 +877,7 @@ void lowp_phase(mcpt_ctx* c, Exec& x, Resident* R, double* G, float* Gf, int sou
     launch_pair_lowp(R->lo_prec, R->lo_variant, 0, p1, R->d_pairs + nl, R->n_pair - nl, R->d_monos, R->d_dif, R->d_Vlo,
                      R->d_lo_off + nl, R->d_Mlo, R->d_mlo_off, G, Gf, x.d_scratch_lo, R->lo_slot, x.grid_lo, R->d_ed2,
                      source, 1, nullptr, cl, x.stream);
-    if (det) launch_reduce_parts(R->d_monos, R->n_mono, R->d_csr_off, R->d_csr, R->d_part, G, R->d_cl, nullptr, x.stream);
+    if (det) launch_reduce_parts(R->d_monos, R->n_mono, R->max_np, R->d_csr_off, R->d_csr, R->d_part, G, R->d_cl, nullptr, x.stream);
 }
 
 void mixed_mono(mcpt_ctx* c, Exec& x, Resident* R, int mode, const double* G, double* Gz, bool lo_out, const Ctrl* ctrl,

@@ -523,7 +523,9 @@ __global__ void reduce_total_kernel(int n_cl, const ClState* __restrict__ cl, Ct
 }
 
 // Deterministic G: G_X[e] = sum over the monomer's stored partial blocks, in
-// pair order (one workgroup per monomer, threads over the np^2 elements).
+// pair order.  Each element is a serial chain of additions over the monomer's pairs, so the work is
+// spread over elements: 256 per workgroup (grid y), eight blocks' reads in flight per chain.  With one workgroup
+// per monomer, which took 256 elements at a time, 80 monomers of up to o5v27 in 738 pairs took 641 us.
 __global__ __launch_bounds__(256) void reduce_parts_kernel(const MonoDesc* __restrict__ monos,
                                                            const int64_t* __restrict__ csr_off,
                                                            const int64_t* __restrict__ csr,
@@ -536,9 +538,19 @@ __global__ __launch_bounds__(256) void reduce_parts_kernel(const MonoDesc* __res
     const int64_t e0 = csr_off[blockIdx.x], e1 = csr_off[blockIdx.x + 1];
     const int64_t nn = (int64_t)d.np * d.np;
     double* g = G + d.mat_off;
-    for (int64_t k = threadIdx.x; k < nn; k += 256) {
+    for (int64_t k = (int64_t)blockIdx.y * 256 + threadIdx.x; k < nn; k += (int64_t)gridDim.y * 256) {
+        const int r = (int)(k / d.np), c = (int)(k - (int64_t)r * d.np);
+        if (r >= d.n || c >= d.n) continue;   // the padding is not stored
         double sum = 0.0;
-        for (int64_t e = e0; e < e1; ++e) sum += part[csr[e] + k];
+        int64_t e = e0;
+        for (; e + 8 <= e1; e += 8) {
+            double p[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) p[u] = part[csr[e + u] + k];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) sum += p[u];
+        }
+        for (; e < e1; ++e) sum += part[csr[e] + k];
         g[k] = sum;
     }
 }
@@ -641,10 +653,11 @@ void launch_energy(const MonoDesc* monos, int n_mono, const double* K, const dou
     hipLaunchKernelGGL(energy_kernel, dim3(n_mono), dim3(kReduceThreads), 0, s, monos, K, M, em2, em2_0, cl);
 }
 
-void launch_reduce_parts(const MonoDesc* monos, int n_mono, const int64_t* csr_off, const int64_t* csr,
+void launch_reduce_parts(const MonoDesc* monos, int n_mono, int max_np, const int64_t* csr_off, const int64_t* csr,
                          const double* part, double* G, const ClState* cl, const Ctrl* ctrl, hipStream_t s) {
     if (n_mono <= 0) return;
-    hipLaunchKernelGGL(reduce_parts_kernel, dim3(n_mono), dim3(256), 0, s, monos, csr_off, csr, part, G, cl, ctrl);
+    const int gy = std::min(512, (int)(((int64_t)max_np * max_np + 255) / 256));
+    hipLaunchKernelGGL(reduce_parts_kernel, dim3(n_mono, gy), dim3(256), 0, s, monos, csr_off, csr, part, G, cl, ctrl);
 }
 
 void launch_reduce_final(int n_cl, const int64_t* cl_mono, const int64_t* cl_pair, const double* em2,

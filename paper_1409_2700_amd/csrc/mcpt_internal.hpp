@@ -174,7 +174,7 @@ void launch_reduce_sweep(int n_cl, const int64_t* cl_mono, double* res, ClState*
                          Ctrl* ctrl, hipStream_t s);
 // G_X = sum of the stored partial blocks of monomer X (csr[csr_off[X] .. csr_off[X+1]):
 // offsets into part, in pair order); skips stopped clusters
-void launch_reduce_parts(const MonoDesc* monos, int n_mono, const int64_t* csr_off, const int64_t* csr,
+void launch_reduce_parts(const MonoDesc* monos, int n_mono, int max_np, const int64_t* csr_off, const int64_t* csr,
                          const double* part, double* G, const ClState* cl, const Ctrl* ctrl, hipStream_t s);
 void launch_reduce_final(int n_cl, const int64_t* cl_mono, const int64_t* cl_pair, const double* em2,
                          const double* em2_0, const double* ed2, ClState* cl, Ctrl* ctrl, hipStream_t s);
