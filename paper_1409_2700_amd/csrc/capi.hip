@@ -11,6 +11,7 @@
 #include <string>
 #include <unordered_set>
 #include <array>
+#include <thread>
 #include <vector>
 
 #include "../../include/mcpt.h"
@@ -499,6 +500,7 @@ void exec_free(mcpt_ctx* c, Exec& x) {
     if (x.d_scratch_lo) (void)hipFree(x.d_scratch_lo);
     if (x.d_ctrl) (void)hipFree(x.d_ctrl);
     if (x.d_flag) (void)hipFree(x.d_flag);
+    if (x.h_out) (void)hipHostFree(x.h_out);
     if (x.h_ctrl) (void)hipHostFree(x.h_ctrl);
     if (x.h_flag) (void)hipHostFree(x.h_flag);
     if (x.own) (void)hipStreamDestroy(x.own);
@@ -515,6 +517,67 @@ void release_resident(mcpt_ctx* c, uint64_t id) {
         c->res.erase(it);
     }
     free_resident(c, r.get());
+}
+
+// Large results to pageable host memory.  The caller's array is usually new, so most of the time goes
+// into the first touch of its pages, one thread of the runtime behind the other with the transfer: 36 ms for
+// the 146 MB of T of 1000 o5v27 monomers, 9 ms this way.  Here each of a few threads takes a part of the array through two
+// pinned chunks of its own, the next transfer in flight while it copies.  Smaller arrays
+// (below kOutMin), and all if there is no staging memory or no thread, go the direct way.
+constexpr int kOutThreads = 8;
+constexpr size_t kOutChunk = size_t(1) << 21;     // bytes; two per thread
+constexpr size_t kOutMin = size_t(1) << 22;
+
+hipError_t copy_out(mcpt_ctx* c, Exec& x, double* dst, const double* src, size_t bytes) {
+    hipStream_t s = x.stream;
+    if (bytes >= kOutMin && !x.h_out &&
+        hipHostMalloc(reinterpret_cast<void**>(&x.h_out), 2 * kOutThreads * kOutChunk, hipHostMallocDefault) != hipSuccess) {
+        (void)hipGetLastError();
+        x.h_out = nullptr;
+    }
+    if (bytes < kOutMin || !x.h_out) return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
+    hipError_t err[kOutThreads];
+    auto part = [&](int t) {
+        hipError_t e = hipSetDevice(c->device);
+        const size_t pages = (bytes + 4095) / 4096;
+        const size_t b0 = std::min(bytes, pages * t / kOutThreads * 4096);
+        const size_t b1 = std::min(bytes, pages * (t + 1) / kOutThreads * 4096);
+        char* buf[2] = {reinterpret_cast<char*>(x.h_out) + 2 * t * kOutChunk,
+                        reinterpret_cast<char*>(x.h_out) + (2 * t + 1) * kOutChunk};
+        hipEvent_t ev[2] = {nullptr, nullptr};
+        for (int k = 0; k < 2 && e == hipSuccess; ++k) e = hipEventCreateWithFlags(&ev[k], hipEventDisableTiming);
+        auto fetch = [&](size_t at, int k) {
+            if (at >= b1) return hipSuccess;
+            hipError_t f = hipMemcpyAsync(buf[k], reinterpret_cast<const char*>(src) + at, std::min(kOutChunk, b1 - at),
+                                          hipMemcpyDeviceToHost, s);
+            return f == hipSuccess ? hipEventRecord(ev[k], s) : f;
+        };
+        if (e == hipSuccess) e = fetch(b0, 0);
+        if (e == hipSuccess) e = fetch(b0 + kOutChunk, 1);
+        for (size_t at = b0, k = 0; at < b1 && e == hipSuccess; at += kOutChunk, k ^= 1) {
+            e = hipEventSynchronize(ev[k]);
+            if (e != hipSuccess) break;
+            std::memcpy(reinterpret_cast<char*>(dst) + at, buf[k], std::min(kOutChunk, b1 - at));
+            e = fetch(at + 2 * kOutChunk, (int)k);
+        }
+        if (e != hipSuccess) (void)hipStreamSynchronize(s);   // nothing in flight into the staging memory
+        for (hipEvent_t v : ev)
+            if (v) (void)hipEventDestroy(v);
+        err[t] = e;
+    };
+    std::vector<std::thread> th;
+    int started = 1;   // part 0 is this thread's
+    try {
+        th.reserve(kOutThreads);
+        for (; started < kOutThreads; ++started) th.emplace_back(part, started);
+    } catch (const std::exception&) {   // the parts without a thread follow below
+    }
+    part(0);
+    for (int t = started; t < kOutThreads; ++t) part(t);
+    for (std::thread& t : th) t.join();
+    for (hipError_t e : err)
+        if (e != hipSuccess) return e;
+    return hipSuccess;
 }
 
 // Results of cluster q of a resident problem (q < 0: every cluster, concatenated).
@@ -538,7 +601,7 @@ mcpt_status slice_results(mcpt_ctx* c, Exec& x, Resident* R, int q, double* e_m2
         HIP_TRY(hipGetLastError());
         const int64_t r0 = R->monos[m0].raw_off;
         const int64_t r1 = m1 < R->n_mono ? R->monos[m1].raw_off : R->raw_elems;
-        HIP_TRY(hipMemcpyAsync(t_amp, R->d_raw + r0, (r1 - r0) * sizeof(double), hipMemcpyDeviceToHost, s));
+        HIP_TRY(copy_out(c, x, t_amp, R->d_raw + r0, (r1 - r0) * sizeof(double)));
     }
     HIP_TRY(hipStreamSynchronize(s));
     for (int64_t k = 0; k < m1 - m0; ++k) {
@@ -2618,18 +2681,17 @@ mcpt_status mcpt_dimer_tau(mcpt_ctx* c, uint64_t id, double* tau) {
     if (!R->dimer) return fail(MCPT_ERR_INVALID, "problem has no dimer-internal terms attached");
     if (!R->has_result) return fail(MCPT_ERR_INVALID, "problem has no result (not run, or diverged)");
     HIP_TRY(hipSetDevice(c->device));
-    std::vector<double> h((size_t)R->dimer_tau_elems);
-    if (R->dimer_tau_elems > 0)
-        HIP_TRY(hipMemcpyAsync(h.data(), R->d_Tau, R->dimer_tau_elems * sizeof(double), hipMemcpyDeviceToHost,
-                               c->main.stream));
+    // pair p (caller order) is stored npx x npy at its tau_off, row (i,a) = i vx + a, column (j,b) = j vy + b;
+    // the caller's blocks lie as V's.  S, formed anew from Tau in every sweep, takes the compact copy and is
+    // cleared again, since the pair kernels also read its padding.  79 MB (540 pairs of 135 x 135): 14 ms on a
+    // first call and 7.2 on later ones; 23 and 10.5 through a host copy of the padded Tau, packed there by rows.
+    launch_unpad_tau(R->d_pairs, R->n_pair, R->d_dd, R->d_Tau, R->d_S, c->main.stream);
+    HIP_TRY(hipGetLastError());
+    const hipError_t e =
+        R->v_elems > 0 ? copy_out(c, c->main, tau, R->d_S, R->v_elems * sizeof(double)) : hipSuccess;
+    launch_fill(R->d_S, R->dimer_tau_elems, 0.0, c->main.stream);
+    HIP_TRY(e);
     HIP_TRY(hipStreamSynchronize(c->main.stream));
-    // pair p (caller order) is stored npx x npy at its tau_off, row (i,a) = i vx + a, column (j,b) = j vy + b
-    int64_t out = 0;
-    for (const DimerDesc& d : R->dimer_desc) {
-        for (int r = 0; r < d.nx; ++r)
-            std::memcpy(tau + out + (int64_t)r * d.ny, h.data() + d.tau_off + (int64_t)r * d.npy, d.ny * sizeof(double));
-        out += (int64_t)d.nx * d.ny;
-    }
     return MCPT_OK;
 }
 

@@ -40,6 +40,17 @@ __global__ void pack_kernel(const MonoDesc* __restrict__ monos, const double* __
     }
 }
 
+__global__ void unpad_tau_kernel(const PairDesc* __restrict__ pairs, const DimerDesc* __restrict__ dd,
+                                 const double* __restrict__ tau, double* __restrict__ out) {
+    const PairDesc pd = pairs[blockIdx.x];
+    const DimerDesc& e = dd[pd.orig];
+    const int ny = e.ny, nn = e.nx * ny;
+    for (int k = threadIdx.x; k < nn; k += blockDim.x) {
+        const int r = k / ny;
+        out[pd.v_off + k] = tau[e.tau_off + (int64_t)r * e.npy + (k - r * ny)];
+    }
+}
+
 __global__ void nonfinite_kernel(const double* __restrict__ p, int64_t n, int32_t* flag) {
     int bad = 0;
     for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n;
@@ -585,6 +596,12 @@ void launch_scale_blocks(const int64_t* off, const int64_t* len, const double* f
                          hipStream_t s) {
     if (n <= 0) return;
     hipLaunchKernelGGL(scale_blocks_kernel, dim3((unsigned)n), dim3(256), 0, s, off, len, f, V);
+}
+
+void launch_unpad_tau(const PairDesc* pairs, int64_t n_pair, const DimerDesc* dd, const double* tau, double* out,
+                      hipStream_t s) {
+    if (n_pair <= 0) return;
+    hipLaunchKernelGGL(unpad_tau_kernel, dim3((unsigned)n_pair), dim3(256), 0, s, pairs, dd, tau, out);
 }
 
 void launch_nonfinite(const double* p, int64_t n, int32_t* flag, hipStream_t s) {

@@ -149,6 +149,9 @@ void launch_pack(const MonoDesc* monos, int n_mono, const double* raw, double* p
                  int max_n, hipStream_t s);
 void launch_unpack(const MonoDesc* monos, int n_mono, const double* packed, double* raw,
                    int max_n, hipStream_t s);
+// Tau of every pair from its padded place (dd, by caller index) to out + the pair's V offset, nX x nY
+void launch_unpad_tau(const PairDesc* pairs, int64_t n_pair, const DimerDesc* dd, const double* tau, double* out,
+                      hipStream_t s);
 void launch_nonfinite(const double* p, int64_t n, int32_t* flag, hipStream_t s);
 // V[off[b] .. off[b] + len[b]) *= f[b] for b < n
 void launch_scale_blocks(const int64_t* off, const int64_t* len, const double* f, int64_t n, double* V,

@@ -162,6 +162,7 @@ struct Exec {
     int grid_cap = 0;                   // > 0: FP64 pair-kernel grids limited to the slots that fit
     void* d_scratch_lo = nullptr;       // reduced-precision Tau and Tau^T
     size_t scratch_lo_bytes = 0;
+    double* h_out = nullptr;            // pinned staging of large results (copy_out), made on first need
     int grid_lo = 0, grid_lo_lds = 0;   // persistent grids of the reduced-precision kernels
     Timing timing;
     size_t reserved = 0;                // HBM reserved by admission for the upload in progress (mu)
