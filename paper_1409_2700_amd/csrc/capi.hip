@@ -52,6 +52,10 @@ void free_lowp(mcpt_ctx* c, Resident* r) {
     r->lo_prec = 0;
     r->d_Vlo = r->d_Mlo = nullptr;
     r->d_lo_off = r->d_mlo_off = nullptr;
+    r->lo_plan = false;
+    r->lo_tau.clear();
+    r->lo_g.clear();
+    r->lo_n.clear();
     r->d_R = r->d_Dl = nullptr;
     r->d_G32[0] = r->d_G32[1] = nullptr;
 }
@@ -901,8 +905,76 @@ mcpt_status ensure_lowp(mcpt_ctx* c, Exec& x, Resident* R, int prec) {
     return MCPT_OK;
 }
 
+// Task lists of the two-launch form for the reduced-precision pairs read from L2: chunks whose Tau and Tau^T fit
+// `bytes` of scratch, pair k of a chunk on XCD k % 8.  Without memory for them the pairs
+// keep to the one-launch kernel.
+void ensure_lo_plan(mcpt_ctx* c, Exec& x, Resident* R, int prec, size_t bytes) {
+    if (R->lo_plan || R->n_pair == R->lo_n_lds) return;
+    const int64_t first = R->lo_n_lds, n = R->n_pair - first, room = (int64_t)(bytes / (prec == MCPT_BF16 ? 2 : 4));
+    const int kc = lowp_chunk(prec);
+    auto elems = [&](int64_t k) {
+        const PairDesc& d = R->pairs[first + k];
+        const MonoDesc &dx = R->monos[d.x], &dy = R->monos[d.y];
+        auto ld = [kc](int m) { return (int64_t)((m + kc - 1) / kc * kc); };
+        return dx.np * ld(dy.n) + dy.np * ld(dx.n);
+    };
+    std::vector<int32_t> xpair, pre_tau, pre_g;
+    std::vector<int64_t> off;
+    struct Chunk {
+        size_t x, p;
+        int m;
+        std::array<int, 9> xbeg;
+    };
+    std::vector<Chunk> chunks;
+    for (int64_t k0 = 0; k0 < n;) {
+        Chunk b{xpair.size(), pre_tau.size(), 0, {}};
+        for (int64_t sum = 0; k0 + b.m < n && b.m < (1 << 20) && (sum += elems(k0 + b.m)) <= room;) ++b.m;
+        if (b.m == 0) return;   // never: one slot of the largest pair fits
+        int64_t o = 0;
+        int32_t tt = 0, tg = 0;
+        for (int xc = 0; xc < 8; ++xc) {
+            b.xbeg[xc] = (int)(xpair.size() - b.x);
+            for (int k = xc; k < b.m; k += 8) {
+                const PairDesc& d = R->pairs[first + k0 + k];
+                const int npX = R->monos[d.x].np, npY = R->monos[d.y].np;
+                xpair.push_back((int32_t)(first + k0 + k));
+                off.push_back(o);
+                pre_tau.push_back(tt);
+                pre_g.push_back(tg);
+                o += elems(k0 + k);
+                tt += lowp_tau_tasks(npX, npY);
+                tg += lowp_g_tasks(npX, npY);
+            }
+        }
+        b.xbeg[8] = b.m;
+        pre_tau.push_back(tt);
+        pre_g.push_back(tg);
+        k0 += b.m;
+        chunks.push_back(b);
+    }
+    void* pv[4] = {};
+    const void* src[4] = {xpair.data(), off.data(), pre_tau.data(), pre_g.data()};
+    const size_t sz[4] = {xpair.size() * 4, off.size() * 8, pre_tau.size() * 4, pre_g.size() * 4};
+    for (int i = 0; i < 4; ++i)
+        if (lo_alloc(c, x, R, &pv[i], sz[i]) != MCPT_OK ||
+            hipMemcpy(pv[i], src[i], sz[i], hipMemcpyHostToDevice) != hipSuccess)
+            return;
+    for (const Chunk& b : chunks) {
+        GlbTasks t{static_cast<int32_t*>(pv[0]) + b.x, static_cast<int64_t*>(pv[1]) + b.x,
+                   static_cast<int32_t*>(pv[2]) + b.p, {}};
+        for (int i = 0; i < 9; ++i) t.xbeg[i] = b.xbeg[i];
+        GlbTasks g = t;
+        g.pre = static_cast<int32_t*>(pv[3]) + b.p;
+        R->lo_tau.push_back(t);
+        R->lo_g.push_back(g);
+        R->lo_n.push_back(b.m);
+    }
+    R->lo_plan = true;
+    R->lo_plan_bytes = bytes;
+}
+
 // Per-stream scratch of the reduced-precision pair kernel (Tau and Tau^T per workgroup).
-mcpt_status ensure_scratch_lo(mcpt_ctx* c, Exec& x, const Resident* R, int prec) {
+mcpt_status ensure_scratch_lo(mcpt_ctx* c, Exec& x, Resident* R, int prec) {
     const size_t es = prec == MCPT_BF16 ? 2 : 4;
     x.grid_lo = std::max(8, c->n_cu * pair_lowp_blocks_per_cu(prec, R->lo_variant, 0) / 8 * 8);
     x.grid_lo_lds = R->lo_n_lds ? std::max(8, c->n_cu * pair_lowp_blocks_per_cu(prec, R->lo_variant, R->lo_lds_bytes) / 8 * 8)
@@ -921,6 +993,7 @@ mcpt_status ensure_scratch_lo(mcpt_ctx* c, Exec& x, const Resident* R, int prec)
         }
         x.scratch_lo_bytes = need;
     }
+    ensure_lo_plan(c, x, R, prec, need);
     return MCPT_OK;
 }
 
@@ -937,6 +1010,16 @@ void lowp_phase(mcpt_ctx* c, Exec& x, Resident* R, double* G, float* Gf, int sou
     launch_pair_lowp(R->lo_prec, R->lo_variant, R->lo_lds_bytes, p0, R->d_pairs, nl, R->d_monos, R->d_dif, R->d_Vlo,
                      R->d_lo_off, R->d_Mlo, R->d_mlo_off, G, Gf, x.d_scratch_lo, R->lo_slot, x.grid_lo_lds, R->d_ed2,
                      source, 1, nullptr, cl, x.stream);
+    // pairs read from L2: two launches per chunk.  Not with stored partials, which the one-launch kernel writes
+    // and whose E_D2 repeats bitwise (the split form adds it with atomics).
+    if (R->lo_plan && !det && x.scratch_lo_bytes >= R->lo_plan_bytes) {
+        const int grid = std::max(8, 2 * c->n_cu / 8 * 8);
+        for (size_t k = 0; k < R->lo_n.size(); ++k)
+            launch_pair_lowp_split(R->lo_prec, R->lo_tau[k], R->lo_g[k], R->lo_n[k], R->d_pairs, R->d_monos, R->d_dif,
+                                   R->d_Vlo, R->d_lo_off, R->d_Mlo, R->d_mlo_off, G, Gf, x.d_scratch_lo, grid,
+                                   R->d_ed2, source, cl, x.stream);
+        return;
+    }
     launch_pair_lowp(R->lo_prec, R->lo_variant, 0, p1, R->d_pairs + nl, R->n_pair - nl, R->d_monos, R->d_dif, R->d_Vlo,
                      R->d_lo_off + nl, R->d_Mlo, R->d_mlo_off, G, Gf, x.d_scratch_lo, R->lo_slot, x.grid_lo, R->d_ed2,
                      source, 1, nullptr, cl, x.stream);

@@ -40,6 +40,19 @@ __global__ void pack_kernel(const MonoDesc* __restrict__ monos, const double* __
     }
 }
 
+// E_D2 of the listed pairs of live clusters set to zero before their Tau tasks add to it
+__global__ __launch_bounds__(256) void zero_ed2_kernel(const PairDesc* __restrict__ pairs,
+                                                            const int32_t* __restrict__ xpair, int n,
+                                                            double* __restrict__ ed2, const Ctrl* __restrict__ ctrl,
+                                                            const ClState* __restrict__ cl) {
+    if (ctrl && ctrl->done) return;
+    const int k = blockIdx.x * 256 + threadIdx.x;
+    if (k >= n) return;
+    const PairDesc pd = pairs[xpair[k]];
+    if (cl && cl[pd.cluster].done) return;
+    ed2[pd.orig] = 0.0;
+}
+
 __global__ void unpad_tau_kernel(const PairDesc* __restrict__ pairs, const DimerDesc* __restrict__ dd,
                                  const double* __restrict__ tau, double* __restrict__ out) {
     const PairDesc pd = pairs[blockIdx.x];
@@ -208,7 +221,7 @@ __global__ __launch_bounds__(kMonoThreads) void monomer_kernel(
                 has_lo = true;
             }
         }
-        if (Ml && has_lo) Ml[(int64_t)r * ldl + c] = (E)(float)lo;
+        if (Ml && has_lo) Ml[lo_at<E>(ldl, r, c)] = (E)(float)lo;
     }
     if (Gz) {
         GT* gz = Gz + d.mat_off;
@@ -375,8 +388,8 @@ __global__ __launch_bounds__(kMonoThreads) void monomer_blocks_kernel(
                     }
                 }
                 if (Ml && has_lo) {
-                    Ml[(int64_t)r1 * ldl + c1] = (E)(float)lo1;
-                    if (!diag) Ml[(int64_t)r2 * ldl + c2] = (E)(float)lo2;
+                    Ml[lo_at<E>(ldl, r1, c1)] = (E)(float)lo1;
+                    if (!diag) Ml[lo_at<E>(ldl, r2, c2)] = (E)(float)lo2;
                 }
                 if (Gz) {   // the padding is never added to
                     Gz[d.mat_off + e1] = GT(0);
@@ -596,6 +609,12 @@ void launch_scale_blocks(const int64_t* off, const int64_t* len, const double* f
                          hipStream_t s) {
     if (n <= 0) return;
     hipLaunchKernelGGL(scale_blocks_kernel, dim3((unsigned)n), dim3(256), 0, s, off, len, f, V);
+}
+
+void launch_zero_ed2(const PairDesc* pairs, const int32_t* xpair, int n, double* ed2, const Ctrl* ctrl,
+                     const ClState* cl, hipStream_t s) {
+    if (n <= 0) return;
+    hipLaunchKernelGGL(zero_ed2_kernel, dim3((n + 255) / 256), dim3(256), 0, s, pairs, xpair, n, ed2, ctrl, cl);
 }
 
 void launch_unpad_tau(const PairDesc* pairs, int64_t n_pair, const DimerDesc* dd, const double* tau, double* out,

@@ -33,6 +33,16 @@ __host__ __device__ inline int64_t frag_at(int np, int r, int c) {
     return ((int64_t)(r >> 3) * (np >> 3) + (c >> 3)) * 64 + ((c & 7) >> 1) * 16 + (r & 7) * 2 + (c & 1);
 }
 
+// Element (r, k) of a reduced-precision operand kept in the order of its fragments: tiles of 16 rows by a
+// chunk of KC values of k (16 in FP32, 32 in BF16), chunk fastest, inside a tile 16 / sizeof(E) values of k per
+// lane, lane (k / KL) 16 + r.  A fragment load is one contiguous KB (17 cycles of the load path against 38 to 64
+// for 16 rows of 64 bytes).  ld: the row's length, a multiple of KC.
+template <class E>
+__host__ __device__ inline int64_t lo_at(int ld, int r, int k) {
+    constexpr int KL = 16 / (int)sizeof(E), KC = 4 * KL;
+    return ((int64_t)(r >> 4) * (ld / KC) + k / KC) * (16 * KC) + ((k % KC) / KL * 16 + (r & 15)) * KL + k % KL;
+}
+
 // 1 / d for the denominators of Eqs. 60-61 (negative, |d| well above zero):
 // the hardware reciprocal estimate refined by two Newton-Raphson steps
 // r <- r + r (1 - d r), each of which squares the relative error, so the
@@ -152,6 +162,9 @@ void launch_unpack(const MonoDesc* monos, int n_mono, const double* packed, doub
 // Tau of every pair from its padded place (dd, by caller index) to out + the pair's V offset, nX x nY
 void launch_unpad_tau(const PairDesc* pairs, int64_t n_pair, const DimerDesc* dd, const double* tau, double* out,
                       hipStream_t s);
+// E_D2 of the listed pairs of live clusters set to zero before their Tau tasks add to it
+void launch_zero_ed2(const PairDesc* pairs, const int32_t* xpair, int n, double* ed2, const Ctrl* ctrl,
+                     const ClState* cl, hipStream_t s);
 void launch_nonfinite(const double* p, int64_t n, int32_t* flag, hipStream_t s);
 // V[off[b] .. off[b] + len[b]) *= f[b] for b < n
 void launch_scale_blocks(const int64_t* off, const int64_t* len, const double* f, int64_t n, double* V,
@@ -207,6 +220,31 @@ struct GlbTasks {
     const int32_t* pre;     // exclusive prefix of the pairs' task counts (n + 1 entries)
     int xbeg[9];            // XCD x's pairs: xpair[xbeg[x] .. xbeg[x + 1])
 };
+constexpr int kTaskXcds = 8;
+// the pair j of XCD group [b, e) that task t falls in (pre: exclusive prefix of task counts)
+__device__ inline int task_pair(const int32_t* __restrict__ pre, int b, int e, int t) {
+    int lo = b, hi = e - 1;
+    while (lo < hi) {
+        const int mid = (lo + hi + 1) >> 1;
+        if (pre[mid] <= t) lo = mid;
+        else hi = mid - 1;
+    }
+    return lo;
+}
+
+// wave-level task loop shared by the two kernels: f(j, local task) for every task of this wave
+template <int NW, class F>
+__device__ inline void for_glb_tasks(const GlbTasks& T, int wave, F&& f) {
+    const int x = blockIdx.x % kTaskXcds, local = blockIdx.x / kTaskXcds, per = gridDim.x / kTaskXcds;
+    const int b = T.xbeg[x], e = T.xbeg[x + 1];
+    if (b >= e) return;
+    const int t1 = T.pre[e], gw = local * NW + wave, nw = per * NW;
+    for (int t = T.pre[b] + gw; t < t1; t += nw) {
+        const int j = task_pair(T.pre, b, e, t);
+        f(j, t - T.pre[j]);
+    }
+}
+
 // tasks of a pair: Tau blocks SR x SC, G blocks SR^2 + SC^2 (SR = ceil(npX / 48), SC = ceil(npY / 48))
 int glb_tau_tasks(int npX, int npY);
 int glb_g_tasks(int npX, int npY);
@@ -219,6 +257,15 @@ void launch_pair_fp64_split(const GlbTasks& tau_tasks, const GlbTasks& g_tasks, 
 int lowp_chunk(int precision);   // k chunk: rows of low-precision operands are padded to it
 void launch_convert_v(int precision, const PairDesc* pairs, int64_t n_pair, const MonoDesc* monos,
                       const double* V, void* Vlo, const int64_t* lo_off, hipStream_t s);
+// Pairs read from L2 in two launches per chunk, as in FP64 (GlbTasks; tau_off: Tau, then Tau^T); G gets
+// only the blocks at and below the diagonal, with the transposes of those above added.  Not with
+// stored partials.
+int lowp_tau_tasks(int npX, int npY);
+int lowp_g_tasks(int npX, int npY);
+void launch_pair_lowp_split(int precision, const GlbTasks& tau_tasks, const GlbTasks& g_tasks, int n_chunk_pairs,
+                            const PairDesc* pairs, const MonoDesc* monos, const double* dif, const void* Vlo,
+                            const int64_t* lo_off, const void* Mlo, const int64_t* mlo_off, double* G, float* Gf,
+                            void* scratch, int grid, double* ed2, int source, const ClState* cl, hipStream_t s);
 // reduced-precision pair kernel: `variant` selects one of lowp_variants() tile shapes;
 // lds_bytes > 0 selects the LDS-resident-V kernel with that much dynamic LDS
 // (every pair of the launch must need at most that much: lowp_lds_bytes)

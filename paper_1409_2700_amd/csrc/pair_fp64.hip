@@ -1001,31 +1001,6 @@ __global__ __launch_bounds__(kThreadsG, 2) void pair_fp64_glb_kernel(
 // ---------------------------------------------------------------------------
 __device__ inline int sb_count(int tiles) { return (tiles + kSB - 1) / kSB; }
 
-// the pair j of XCD group [b, e) that task t falls in (pre: exclusive prefix of task counts)
-__device__ inline int task_pair(const int32_t* __restrict__ pre, int b, int e, int t) {
-    int lo = b, hi = e - 1;
-    while (lo < hi) {
-        const int mid = (lo + hi + 1) >> 1;
-        if (pre[mid] <= t) lo = mid;
-        else hi = mid - 1;
-    }
-    return lo;
-}
-
-// wave-level task loop shared by the two kernels: f(j, local task) for every task of this wave
-template <class F>
-__device__ inline void for_glb_tasks(const GlbTasks& T, int wave, F&& f) {
-    constexpr int NW = kThreadsG / 64;
-    const int x = blockIdx.x % kXcds, local = blockIdx.x / kXcds, per = gridDim.x / kXcds;
-    const int b = T.xbeg[x], e = T.xbeg[x + 1];
-    if (b >= e) return;
-    const int t1 = T.pre[e], gw = local * NW + wave, nw = per * NW;
-    for (int t = T.pre[b] + gw; t < t1; t += nw) {
-        const int j = task_pair(T.pre, b, e, t);
-        f(j, t - T.pre[j]);
-    }
-}
-
 // Tau = D_XY * (V + M_X V + V M_Y^T) on tiles (r0.., c0..) into the pair's Tau slot; returns the
 // lane's part of <V, Tau>
 template <int NR, int NC>
@@ -1066,19 +1041,6 @@ __device__ inline double tau_block_glb(const PairView& p, double* tau, int r0, i
     return epart;
 }
 
-// E_D2 of the chunk's pairs of live clusters set to zero before their Tau tasks add to it
-__global__ __launch_bounds__(256) void glb_zero_ed2_kernel(const PairDesc* __restrict__ pairs,
-                                                            const int32_t* __restrict__ xpair, int n,
-                                                            double* __restrict__ ed2, const Ctrl* __restrict__ ctrl,
-                                                            const ClState* __restrict__ cl) {
-    if (ctrl && ctrl->done) return;
-    const int k = blockIdx.x * 256 + threadIdx.x;
-    if (k >= n) return;
-    const PairDesc pd = pairs[xpair[k]];
-    if (cl && cl[pd.cluster].done) return;
-    ed2[pd.orig] = 0.0;
-}
-
 __global__ __launch_bounds__(kThreadsG, 2) void pair_glb_tau_kernel(
     GlbTasks T, const PairDesc* __restrict__ pairs, const MonoDesc* __restrict__ monos,
     const double* __restrict__ dif, const double* __restrict__ V, const double* __restrict__ M,
@@ -1086,7 +1048,7 @@ __global__ __launch_bounds__(kThreadsG, 2) void pair_glb_tau_kernel(
     const ClState* __restrict__ cl) {
     if (ctrl && ctrl->done) return;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for_glb_tasks(T, wave, [&](int j, int lt) {
+    for_glb_tasks<kThreadsG / 64>(T, wave, [&](int j, int lt) {
         const PairDesc pd = pairs[T.xpair[j]];
         if (cl && cl[pd.cluster].done) return;   // uniform over the wave
         const PairView p = make_view(pd, monos, dif, V, M, nullptr);
@@ -1126,7 +1088,7 @@ __global__ __launch_bounds__(kThreadsG, 2) void pair_glb_g_kernel(
     const ClState* __restrict__ cl) {
     if (ctrl && ctrl->done) return;
     const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-    for_glb_tasks(T, wave, [&](int j, int lt) {
+    for_glb_tasks<kThreadsG / 64>(T, wave, [&](int j, int lt) {
         const PairDesc pd = pairs[T.xpair[j]];
         if (cl && cl[pd.cluster].done) return;
         const PairView p = make_view(pd, monos, dif, V, M, G);
@@ -1162,8 +1124,7 @@ void launch_pair_fp64_split(const GlbTasks& tau_tasks, const GlbTasks& g_tasks, 
                             const double* M, double* G, double* scratch, int grid, double* ed2, int couple,
                             const Ctrl* ctrl, const ClState* cl, hipStream_t s) {
     if (n_chunk_pairs <= 0) return;
-    hipLaunchKernelGGL(glb_zero_ed2_kernel, dim3((n_chunk_pairs + 255) / 256), dim3(256), 0, s, pairs,
-                       tau_tasks.xpair, n_chunk_pairs, ed2, ctrl, cl);
+    launch_zero_ed2(pairs, tau_tasks.xpair, n_chunk_pairs, ed2, ctrl, cl, s);
     hipLaunchKernelGGL(pair_glb_tau_kernel, dim3(grid), dim3(kThreadsG), 0, s, tau_tasks, pairs, monos, dif, V, M,
                        scratch, ed2, couple, ctrl, cl);
     if (couple)

@@ -3,8 +3,8 @@
 //
 // Same products as the FP64 pair phase (Eq. 59 Tau, Eq. 55 E_D2, the Eq. 58
 // contractions G_X += Tau V^T, G_Y += Tau^T V), with:
-//   * operands stored so the contraction index k is contiguous in every one of
-//     them: V and V^T (per pair, converted once per problem), M (per monomer,
+//   * operands stored in the order of the fragments that are read from them (lo_at),
+//     the contraction index k contiguous within a lane's part of every one of them: V and V^T (per pair, converted once per problem), M (per monomer,
 //     written by the monomer kernel each sweep), Tau and Tau^T (per-workgroup
 //     scratch), each row padded to a multiple of the k chunk and zero there;
 //     every operand fragment is then one 16-byte load per lane;
@@ -87,7 +87,8 @@ __device__ inline typename Lowp<E>::Frag frag(const E* p) {
 
 // Operand sources of a 16 x KC fragment (lane l: row 16*tile + l%16, KL
 // contiguous k from k0 + KL*(l/16)):
-//   Rows: a row-major matrix with k contiguous (global memory or LDS);
+//   Rows: a row-major matrix with k contiguous (LDS);
+//   Frags: a matrix in global memory in fragment order (lo_at);
 //   Cols: the transpose of a row-major LDS matrix (element (row, k) at
 //         p[k * ld + row]), read as KL scalars per lane; every row k of the
 //         chunk must be readable, and rows at or past the matrix's last are
@@ -98,6 +99,17 @@ struct Rows {
     int ld;
     __device__ typename Lowp<E>::Frag operator()(int tile, int k0, int lane) const {
         return frag(p + (int64_t)(tile * 16 + (lane & 15)) * ld + k0 + (lane >> 4) * Lowp<E>::KL);
+    }
+};
+
+template <class E>
+struct Frags {
+    const E* p;
+    int ld, last;   // row length; last tile: a task's tiles past it read it again and are not used
+    __device__ typename Lowp<E>::Frag operator()(int tile, int k0, int lane) const {
+        typedef Lowp<E> L;
+        const int64_t blk = (int64_t)min(tile, last) * (ld / L::KC) + k0 / L::KC;
+        return frag(p + (blk * 64 + lane) * L::KL);
     }
 };
 
@@ -288,7 +300,7 @@ __device__ inline int64_t pair_for(int64_t it, int64_t n_pair) {
 
 // Layout of the reduced-precision copies of a pair (offset lo_off of the pair):
 //   V   npX rows x ldY  (ldY = nY rounded up to the k chunk), then
-//   V^T npY rows x ldX.
+//   V^T npY rows x ldX, both in fragment order (lo_at).
 template <class E>
 __global__ __launch_bounds__(kThreads) void convert_v_kernel(const PairDesc* __restrict__ pairs,
                                                               const MonoDesc* __restrict__ monos,
@@ -301,12 +313,20 @@ __global__ __launch_bounds__(kThreads) void convert_v_kernel(const PairDesc* __r
     const double* v = V + pd.v_off;
     E* vl = Vlo + lo_off[blockIdx.x];
     E* vt = vl + (int64_t)dx.np * ldY;
+    // place idx of a copy: tile of 16 rows, chunk, lane, value (lo_at)
+    auto place = [&](int idx, int ld, int& r, int& k) {
+        const int blk = idx / (16 * L::KC), in = idx - blk * (16 * L::KC), lane = in / L::KL, nch = ld / L::KC;
+        r = blk / nch * 16 + (lane & 15);
+        k = blk % nch * L::KC + (lane >> 4) * L::KL + in % L::KL;
+    };
     for (int idx = threadIdx.x; idx < dx.np * ldY; idx += kThreads) {
-        const int r = idx / ldY, c = idx - r * ldY;
+        int r, c;
+        place(idx, ldY, r, c);
         vl[idx] = L::from((r < dx.n && c < dy.n) ? v[(int64_t)r * dy.n + c] : 0.0);
     }
     for (int idx = threadIdx.x; idx < dy.np * ldX; idx += kThreads) {
-        const int c = idx / ldX, r = idx - c * ldX;
+        int c, r;
+        place(idx, ldX, c, r);
         vt[idx] = L::from((r < dx.n && c < dy.n) ? v[(int64_t)r * dy.n + c] : 0.0);
     }
 }
@@ -371,11 +391,11 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
         if (IN_LDS) {   // stage V with 16-byte copies; padding rows and columns come zero
             constexpr int VE = 16 / sizeof(E);
             typedef uint4 Chunk;
-            const int cy = ldY / VE;
-            for (int idx = threadIdx.x; idx < npX * cy; idx += kThreadsK) {
-                const int r = idx / cy, c = idx - r * cy;
-                *reinterpret_cast<Chunk*>(sV + r * sldY + c * VE) =
-                    *reinterpret_cast<const Chunk*>(V + (int64_t)r * ldY + c * VE);
+            const int nch = ldY / L::KC;
+            for (int idx = threadIdx.x; idx < npX * ldY / VE; idx += kThreadsK) {
+                const int blk = idx >> 6, ln = idx & 63;
+                const int r = blk / nch * 16 + (ln & 15), c = blk % nch * L::KC + (ln >> 4) * VE;
+                *reinterpret_cast<Chunk*>(sV + r * sldY + c) = *reinterpret_cast<const Chunk*>(V + (int64_t)idx * VE);
             }
             if (kTrLds) {
                 // V and Tau rows npX..ldX-1: zero, read as the k padding of the transposed fragments
@@ -387,10 +407,15 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
             __syncthreads();
         }
         auto v_at = [&](int r, int c) -> double {
-            return L::to_d(IN_LDS ? sV[r * sldY + c] : V[(int64_t)r * ldY + c]);
+            return L::to_d(IN_LDS ? sV[r * sldY + c] : V[lo_at<E>(ldY, r, c)]);
         };
         // the four operand roles of V: rows of V (k over Y), rows of V^T (k over X)
-        auto vrows = [&]() { return Rows<E>{IN_LDS ? sV : V, IN_LDS ? sldY : ldY}; };
+        auto vrows = [&]() {
+            if constexpr (IN_LDS) return Rows<E>{sV, sldY};
+            else return Frags<E>{V, ldY, RB - 1};
+        };
+        const Frags<E> fMX{MX, ldX, RB - 1}, fMY{MY, ldY, CB - 1}, fVt{Vt, ldX, CB - 1};
+        const Frags<E> fTau{tau, ldY, RB - 1}, fTauT{tauT, ldX, CB - 1};
 
         // ---- Tau = D_XY * (source V + M_X V + V M_Y^T), E_D2 = 4 <V, Tau> ----
         double epart = 0.0;
@@ -398,10 +423,10 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
             constexpr int NR = decltype(shape)::NR, NC = decltype(shape)::NC;
             f4 acc[NR][NC];
             zero(acc);
-            if constexpr (kTrLds) gemm<E, NR, NC, PD>(Rows<E>{MX, ldX}, ColsTr{sV, sldY}, ldX, r0, c0, lane, acc);   // M_X V
-            else if (IN_LDS) gemm<E, NR, NC, PD>(Rows<E>{MX, ldX}, Cols<E>{sV, sldY}, ldX, r0, c0, lane, acc);
-            else gemm<E, NR, NC, PD>(Rows<E>{MX, ldX}, Rows<E>{Vt, ldX}, ldX, r0, c0, lane, acc);
-            gemm<E, NR, NC, PD>(vrows(), Rows<E>{MY, ldY}, ldY, r0, c0, lane, acc);                        // V M_Y^T
+            if constexpr (kTrLds) gemm<E, NR, NC, PD>(fMX, ColsTr{sV, sldY}, ldX, r0, c0, lane, acc);   // M_X V
+            else if (IN_LDS) gemm<E, NR, NC, PD>(fMX, Cols<E>{sV, sldY}, ldX, r0, c0, lane, acc);
+            else gemm<E, NR, NC, PD>(fMX, fVt, ldX, r0, c0, lane, acc);
+            gemm<E, NR, NC, PD>(vrows(), fMY, ldY, r0, c0, lane, acc);                        // V M_Y^T
             // Epilogue, tile by tile: a tile's energy differences and V values are read
             // before its stores, at the padded indices (V, its copies and the differences
             // are zero-padded, so every read is in bounds), and the padding is masked by
@@ -432,11 +457,11 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
                         tv4[t] = L::from(tv);
                         if (couple) {
                             if (kTrLds) sTau[r * sldY + c] = tv4[t];
-                            else tau[(int64_t)r * ldY + c] = tv4[t];
+                            else tau[lo_at<E>(ldY, r, c)] = tv4[t];
                         }
                     }
                     if (couple && !kTrLds) {   // Tau^T row c, 4 consecutive columns (BF16 reads Tau from LDS)
-                        E* q = tauT + (int64_t)c * ldX + (r0 + i) * 16 + acc_row(lane, 0);
+                        E* q = tauT + lo_at<E>(ldX, c, (r0 + i) * 16 + acc_row(lane, 0));
 #pragma unroll
                         for (int t = 0; t < 4; ++t) q[t] = tv4[t];
                     }
@@ -450,11 +475,11 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
             for (int idx = threadIdx.x; idx < npX * (ldY - npY); idx += kThreadsK) {
                 const int r = idx / (ldY - npY), c = npY + idx % (ldY - npY);
                 if (kTrLds) sTau[r * sldY + c] = L::from(0.0);
-                else tau[(int64_t)r * ldY + c] = L::from(0.0);
+                else tau[lo_at<E>(ldY, r, c)] = L::from(0.0);
             }
             for (int idx = threadIdx.x; !kTrLds && idx < npY * (ldX - npX); idx += kThreadsK) {
                 const int r = idx / (ldX - npX), c = npX + idx % (ldX - npX);
-                tauT[(int64_t)r * ldX + c] = L::from(0.0);
+                tauT[lo_at<E>(ldX, r, c)] = L::from(0.0);
             }
         }
         epart = wave_sum(epart);
@@ -489,14 +514,14 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
                 zero(acc);
                 if (which == 0) {
                     if (kTrLds) gemm<E, NR, NC, PD>(Rows<E>{sTau, sldY}, vrows(), ldY, r0, c0, lane, acc);
-                    else gemm<E, NR, NC, PD>(Rows<E>{tau, ldY}, vrows(), ldY, r0, c0, lane, acc);
+                    else gemm<E, NR, NC, PD>(fTau, vrows(), ldY, r0, c0, lane, acc);
                     atomic_flush(GX, GfX, po.part ? po.part + po.off[pi] : nullptr, npX, nX, r0, c0, lane, acc);
                 } else {
                     if constexpr (kTrLds)   // Tau^T and V, both transposed from the row-major LDS copies
                         gemm<E, NR, NC, PD>(ColsTr{sTau, sldY}, ColsTr{sV, sldY}, ldX, r0, c0, lane, acc);
                     else if (IN_LDS)
-                        gemm<E, NR, NC, PD>(Rows<E>{tauT, ldX}, Cols<E>{sV, sldY}, ldX, r0, c0, lane, acc);
-                    else gemm<E, NR, NC, PD>(Rows<E>{tauT, ldX}, Rows<E>{Vt, ldX}, ldX, r0, c0, lane, acc);
+                        gemm<E, NR, NC, PD>(fTauT, Cols<E>{sV, sldY}, ldX, r0, c0, lane, acc);
+                    else gemm<E, NR, NC, PD>(fTauT, fVt, ldX, r0, c0, lane, acc);
                     atomic_flush(GY, GfY, po.part ? po.part + po.off[pi] + (int64_t)npX * npX : nullptr, npY, nY, r0,
                                  c0, lane, acc);
                 }
@@ -505,6 +530,221 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
         __syncthreads();
     }
     if (sink == 1.2345e30f) ed2[0] = sink;   // keeps the prefetch loads; never true for finite inputs
+}
+
+// ---- pairs read from L2, in two launches per chunk ----
+// What bounds a pair of o8v56 monomers (0.72 GFLOP) is the matrix pipe, once its operands come from L2 in fragment
+// order and the work is spread evenly.  A workgroup per pair did neither: the rows of 16 x 64 bytes cost three
+// times the load path's cycles, and with a few hundred pairs per launch the compute units with one
+// pair more than the others decided its time.  Here a task is a block of up to 4 x 4 tiles of one
+// output, dealt out to the waves of the pair's XCD.  The FP32 pair phase of a batch of 120 monomers of
+// o5v27 and o8v56 (0.21 TFLOP) went from 6.9 to 3.4 ms, 63 TFLOP/s.
+constexpr int kThreadsS = 256;   // four waves, two workgroups per CU: 256 registers per lane
+
+// n tiles cut into ceil(n / 4) segments that differ by at most one
+__host__ __device__ inline int seg_count(int n) { return (n + 3) / 4; }
+__device__ inline void seg(int n, int s, int& first, int& len) {
+    const int k = seg_count(n), q = n / k, rem = n - q * k;
+    first = s * q + min(s, rem);
+    len = q + (s < rem ? 1 : 0);
+}
+
+// f(Shape<NR, NC>) for a block of nr x nc tiles (1 runs as 2, the second tile being the first again)
+template <class F>
+__device__ inline void with_shape(int nr, int nc, F&& f) {
+    auto cols = [&](auto r) {
+        constexpr int NR = decltype(r)::NR;
+        if (nc == 4) f(Shape<NR, 4>{});
+        else if (nc == 3) f(Shape<NR, 3>{});
+        else f(Shape<NR, 2>{});
+    };
+    if (nr == 4) cols(Shape<4, 0>{});
+    else if (nr == 3) cols(Shape<3, 0>{});
+    else cols(Shape<2, 0>{});
+}
+
+template <class E>
+struct LoPair {
+    const E *V, *Vt, *MX, *MY;
+    E *tau, *tauT;
+    const double *dX, *dY;
+    int nX, nY, RB, CB, ldX, ldY;
+};
+
+template <class E>
+__device__ inline LoPair<E> lo_pair(const PairDesc& pd, const MonoDesc* monos, const double* dif, const E* V,
+                                    const E* Mlo, const int64_t* mlo_off, E* tau) {
+    typedef Lowp<E> L;
+    const MonoDesc dx = monos[pd.x], dy = monos[pd.y];
+    const int ldX = (dx.n + L::KC - 1) / L::KC * L::KC, ldY = (dy.n + L::KC - 1) / L::KC * L::KC;
+    return {V, V + (int64_t)dx.np * ldY, Mlo + mlo_off[pd.x], Mlo + mlo_off[pd.y], tau, tau + (int64_t)dx.np * ldY,
+            dif + dx.dif_off, dif + dy.dif_off, dx.n, dy.n, dx.np / 16, dy.np / 16, ldX, ldY};
+}
+
+template <class E>
+struct alignas(4 * sizeof(E)) Quad {
+    E v[4];
+};
+
+// Tau = D_XY * (source V + M_X V + V M_Y^T) on nr x nc tiles from (r0, c0) into Tau and Tau^T; the lane's part
+// of <V, Tau>.  A tile's accumulator (4 rows of a column per lane) is the order of Tau^T and V^T, which
+// take one load and one store; Tau is turned in the wave's LDS square first.
+template <class E, int NR, int NC>
+__device__ inline double lo_tau_block(const LoPair<E>& p, E* sq, int r0, int nr, int c0, int nc, int source, int lane) {
+    typedef Lowp<E> L;
+    constexpr int kRow = 16 + 16 / (int)sizeof(E);
+    f4 acc[NR][NC];
+    zero(acc);
+    gemm<E, NR, NC, 1>(Frags<E>{p.MX, p.ldX, p.RB - 1}, Frags<E>{p.Vt, p.ldX, p.CB - 1}, p.ldX, r0, c0, lane, acc);
+    gemm<E, NR, NC, 1>(Frags<E>{p.V, p.ldY, p.RB - 1}, Frags<E>{p.MY, p.ldY, p.CB - 1}, p.ldY, r0, c0, lane, acc);
+    const int g4 = (lane >> 4) * 4, q = lane & 15;
+    double epart = 0.0;
+#pragma unroll
+    for (int j = 0; j < NC; ++j)
+#pragma unroll
+        for (int i = 0; i < NR; ++i) {
+            if (i < nr && j < nc) {
+                int rt = r0 + i, ct = c0 + j;
+                asm volatile("" : "+s"(rt), "+s"(ct));   // this tile's addresses here, not all tiles' ahead (registers)
+                const int c = ct * 16 + q, r = rt * 16 + g4;
+                const int64_t at = lo_at<E>(p.ldX, c, r);
+                const Quad<E> v4 = *reinterpret_cast<const Quad<E>*>(p.Vt + at);
+                const double dc = p.dY[c];
+                Quad<E> t4;
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const bool ok = r + t < p.nX && c < p.nY;
+                    const double v = L::to_d(v4.v[t]);
+                    const double tv = ok ? recip(p.dX[r + t] + dc) * ((source ? v : 0.0) + (double)acc[i][j][t]) : 0.0;
+                    epart += ok ? v * tv : 0.0;
+                    t4.v[t] = L::from(tv);
+                    sq[(g4 + t) * kRow + q] = t4.v[t];
+                }
+                *reinterpret_cast<Quad<E>*>(p.tauT + at) = t4;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                const Quad<E> w4 = *reinterpret_cast<const Quad<E>*>(sq + q * kRow + g4);
+                *reinterpret_cast<Quad<E>*>(p.tau + lo_at<E>(p.ldY, rt * 16 + q, ct * 16 + g4)) = w4;
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+            }
+            __builtin_amdgcn_sched_barrier(0);   // the next tile's loads after this tile's work (registers)
+        }
+    if (sizeof(E) == 2) {   // zero the k padding past the last tile: half a chunk where the tiles are odd
+        Quad<E> z;
+#pragma unroll
+        for (int t = 0; t < 4; ++t) z.v[t] = L::from(0.0);
+        if (p.CB * 16 < p.ldY && c0 + nc == p.CB)
+            for (int i = 0; i < nr; ++i)
+                *reinterpret_cast<Quad<E>*>(p.tau + lo_at<E>(p.ldY, (r0 + i) * 16 + q, p.CB * 16 + g4)) = z;
+        if (p.RB * 16 < p.ldX && r0 + nr == p.RB)
+            for (int j = 0; j < nc; ++j)
+                *reinterpret_cast<Quad<E>*>(p.tauT + lo_at<E>(p.ldX, (c0 + j) * 16 + q, p.RB * 16 + g4)) = z;
+    }
+    return epart;
+}
+
+template <class E>
+__global__ __launch_bounds__(kThreadsS, 2) void lowp_tau_kernel(
+    GlbTasks T, const PairDesc* __restrict__ pairs, const MonoDesc* __restrict__ monos,
+    const double* __restrict__ dif, const E* __restrict__ Vlo, const int64_t* __restrict__ lo_off,
+    const E* __restrict__ Mlo, const int64_t* __restrict__ mlo_off, E* __restrict__ scratch,
+    double* __restrict__ ed2, int source, const ClState* __restrict__ cl) {
+    __shared__ __align__(16) E square[kThreadsS / 64][16 * (16 + 16 / sizeof(E))];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    for_glb_tasks<kThreadsS / 64>(T, wave, [&](int j, int lt) {
+        const int pi = T.xpair[j];
+        const PairDesc pd = pairs[pi];
+        if (cl && cl[pd.cluster].done) return;   // uniform over the wave
+        const LoPair<E> p = lo_pair<E>(pd, monos, dif, Vlo + lo_off[pi], Mlo, mlo_off, scratch + T.tau_off[j]);
+        const int SC = seg_count(p.CB);
+        int r0, nr, c0, nc;
+        seg(p.RB, lt / SC, r0, nr);
+        seg(p.CB, lt % SC, c0, nc);
+        double epart = 0.0;
+        with_shape(nr, nc, [&](auto s) {
+            epart = lo_tau_block<E, decltype(s)::NR, decltype(s)::NC>(p, square[wave], r0, nr, c0, nc, source, lane);
+        });
+        epart = wave_sum(epart);
+        if (lane == 0) unsafeAtomicAdd(ed2 + pd.orig, 4.0 * epart);
+    });
+}
+
+// G_X += Tau V^T (which = 0) or G_Y += Tau^T V (1): G enters the monomer equation as G + G^T only, so block (i, j)
+// below the diagonal also takes the transpose of block (j, i), V Tau^T, and half of the atomic
+// additions (206 cycles of the store path per 64 values in FP64) fall away.  The two products are
+// added in FP64 where G is.
+template <class E, int NR, int NC>
+__device__ inline void lo_g_block(const Frags<E>& tau, const Frags<E>& v, int K, double* G, float* Gf, int ld, int n,
+                                  int r0, int nr, int q0, int nc, int lane) {
+    constexpr bool kTwo = sizeof(E) == 4;
+    f4 acc[NR][NC], acc2[kTwo ? NR : 1][kTwo ? NC : 1];
+    zero(acc);
+    zero(acc2);
+    gemm<E, NR, NC, 1>(tau, v, K, r0, q0, lane, acc);
+    if (r0 != q0) {
+        if constexpr (kTwo) gemm<E, NR, NC, 1>(v, tau, K, r0, q0, lane, acc2);
+        else gemm<E, NR, NC, 1>(v, tau, K, r0, q0, lane, acc);
+    }
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+            if (i >= nr || j >= nc) continue;
+            const int c = (q0 + j) * 16 + acc_col(lane);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int r = (r0 + i) * 16 + acc_row(lane, t);
+                if (r < n && c < n) {
+                    if (Gf) unsafeAtomicAdd(Gf + (int64_t)r * ld + c, acc[i][j][t] + (kTwo ? acc2[i][j][t] : 0.f));
+                    else unsafeAtomicAdd(G + (int64_t)r * ld + c,
+                                         (double)acc[i][j][t] + (kTwo ? (double)acc2[i][j][t] : 0.0));
+                }
+            }
+        }
+}
+
+template <class E>
+__global__ __launch_bounds__(kThreadsS, 2) void lowp_g_kernel(
+    GlbTasks T, const PairDesc* __restrict__ pairs, const MonoDesc* __restrict__ monos,
+    const double* __restrict__ dif, const E* __restrict__ Vlo, const int64_t* __restrict__ lo_off,
+    const E* __restrict__ Mlo, const int64_t* __restrict__ mlo_off, double* __restrict__ G, float* __restrict__ Gf,
+    E* __restrict__ scratch, const ClState* __restrict__ cl) {
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+    for_glb_tasks<kThreadsS / 64>(T, wave, [&](int j, int lt) {
+        const int pi = T.xpair[j];
+        const PairDesc pd = pairs[pi];
+        if (cl && cl[pd.cluster].done) return;
+        const LoPair<E> p = lo_pair<E>(pd, monos, dif, Vlo + lo_off[pi], Mlo, mlo_off, scratch + T.tau_off[j]);
+        const int SR = seg_count(p.RB), nx = SR * (SR + 1) / 2, which = lt < nx ? 0 : 1;
+        int u = which ? lt - nx : lt, i = 0;   // row i of the triangle: blocks (i, 0) .. (i, i)
+        while (u > i) u -= ++i;
+        const int n = which ? p.CB : p.RB;
+        int r0, nr, q0, nc;
+        seg(n, i, r0, nr);
+        seg(n, u, q0, nc);
+        const int64_t off = monos[which ? pd.y : pd.x].mat_off;
+        const Frags<E> ft = which ? Frags<E>{p.tauT, p.ldX, n - 1} : Frags<E>{p.tau, p.ldY, n - 1};
+        const Frags<E> fv = which ? Frags<E>{p.Vt, p.ldX, n - 1} : Frags<E>{p.V, p.ldY, n - 1};
+        with_shape(nr, nc, [&](auto s) {
+            lo_g_block<E, decltype(s)::NR, decltype(s)::NC>(ft, fv, which ? p.ldX : p.ldY, G ? G + off : nullptr,
+                                                            Gf ? Gf + off : nullptr, n * 16, which ? p.nY : p.nX, r0,
+                                                            nr, q0, nc, lane);
+        });
+    });
+}
+
+template <class E>
+void launch_split(const GlbTasks& tt, const GlbTasks& tg, const PairDesc* pairs, const MonoDesc* monos,
+                  const double* dif, const void* Vlo, const int64_t* lo_off, const void* Mlo, const int64_t* mlo_off,
+                  double* G, float* Gf, void* scratch, int grid, double* ed2, int source, const ClState* cl,
+                  hipStream_t s) {
+    const E *v = static_cast<const E*>(Vlo), *m = static_cast<const E*>(Mlo);
+    E* sc = static_cast<E*>(scratch);
+    hipLaunchKernelGGL(lowp_tau_kernel<E>, dim3(grid), dim3(kThreadsS), 0, s, tt, pairs, monos, dif, v, lo_off, m,
+                       mlo_off, sc, ed2, source, cl);
+    hipLaunchKernelGGL(lowp_g_kernel<E>, dim3(grid), dim3(kThreadsS), 0, s, tg, pairs, monos, dif, v, lo_off, m,
+                       mlo_off, G, Gf, sc, cl);
 }
 
 template <class E, int V, bool IN_LDS>
@@ -529,6 +769,23 @@ const void* lowp_kernel(int precision, int variant, bool in_lds) {
 int lowp_variant_threads(int variant) { return kVariants[variant].nw * 64; }
 
 }  // namespace
+
+int lowp_tau_tasks(int npX, int npY) { return seg_count(npX / 16) * seg_count(npY / 16); }
+
+int lowp_g_tasks(int npX, int npY) {
+    const int sr = seg_count(npX / 16), sc = seg_count(npY / 16);
+    return sr * (sr + 1) / 2 + sc * (sc + 1) / 2;
+}
+
+void launch_pair_lowp_split(int precision, const GlbTasks& tau_tasks, const GlbTasks& g_tasks, int n_chunk_pairs,
+                            const PairDesc* pairs, const MonoDesc* monos, const double* dif, const void* Vlo,
+                            const int64_t* lo_off, const void* Mlo, const int64_t* mlo_off, double* G, float* Gf,
+                            void* scratch, int grid, double* ed2, int source, const ClState* cl, hipStream_t s) {
+    if (n_chunk_pairs <= 0) return;
+    launch_zero_ed2(pairs, tau_tasks.xpair, n_chunk_pairs, ed2, nullptr, cl, s);
+    const auto launch = precision == 2 ? launch_split<__bf16> : launch_split<float>;
+    launch(tau_tasks, g_tasks, pairs, monos, dif, Vlo, lo_off, Mlo, mlo_off, G, Gf, scratch, grid, ed2, source, cl, s);
+}
 
 int lowp_chunk(int precision) { return precision == 2 ? Lowp<__bf16>::KC : Lowp<float>::KC; }
 

@@ -67,6 +67,11 @@ struct Resident {
     float* d_G32[2] = {nullptr, nullptr};   // BF16 sweeps: G accumulated in FP32 (double-buffered like d_G)
     int64_t lo_slot = 0;          // elements of one low-precision Tau + Tau^T scratch slot
     double lo_v_bytes = 0.0;      // bytes of the low-precision V and V^T
+    // its pairs read from L2, chunk by chunk (the Tau of a chunk fits lo_plan_bytes of scratch)
+    bool lo_plan = false;
+    size_t lo_plan_bytes = 0;
+    std::vector<GlbTasks> lo_tau, lo_g;
+    std::vector<int> lo_n;
     std::vector<void*> lo_allocations;
     size_t lo_bytes = 0;
     // singles (made on the first mcpt_singles; freed with the problem): vectors in the padded
