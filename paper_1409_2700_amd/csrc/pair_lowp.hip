@@ -153,7 +153,7 @@ struct ColsTr {
 // fragments of the PD chunks after the current one in flight (a ring of PD
 // register slots, the loop unrolled by PD so every slot index is static).
 template <class E, int NR, int NC, int PD, class SA, class SB_>
-__device__ inline void gemm(const SA& A, const SB_& B, int K, int m0, int n0, int lane, f4 (&acc)[NR][NC]) {
+__device__ __forceinline__ void gemm(const SA& A, const SB_& B, int K, int m0, int n0, int lane, f4 (&acc)[NR][NC]) {
     typedef Lowp<E> L;
     typename L::Frag ra[PD][NR], rb[PD][NC];
 #pragma unroll
@@ -191,7 +191,7 @@ __device__ inline void gemm(const SA& A, const SB_& B, int K, int m0, int n0, in
 }
 
 template <int NR, int NC>
-__device__ inline void zero(f4 (&acc)[NR][NC]) {
+__device__ __forceinline__ void zero(f4 (&acc)[NR][NC]) {
 #pragma unroll
     for (int i = 0; i < NR; ++i)
 #pragma unroll
@@ -289,13 +289,27 @@ __device__ inline double wave_sum(double x) {
     return x;
 }
 
-__device__ inline int64_t pair_for(int64_t it, int64_t n_pair) {
+// The pairs of a workgroup: its XCD's share of the list in runs of `run` pairs, dealt round-robin
+struct PairRuns {
+    int64_t begin, end, first, step;
+    int run;
+    __device__ int64_t at(int64_t it) const {   // INT64_MAX past the last
+        const int64_t p = begin + (first + it / run * step) * run + it % run;
+        return p < end ? p : INT64_MAX;
+    }
+};
+
+// longest > 1: runs of up to that many pairs, at least eight runs per workgroup
+__device__ inline PairRuns pair_runs(int64_t n_pair, int longest) {
     const int g = gridDim.x;
-    if (g % kXcds != 0) return (int64_t)blockIdx.x + it * g;
-    const int xcd = blockIdx.x % kXcds, local = blockIdx.x / kXcds, per = g / kXcds;
-    const int64_t begin = n_pair * xcd / kXcds, end = n_pair * (xcd + 1) / kXcds;
-    const int64_t p = begin + local + it * per;
-    return p < end ? p : INT64_MAX;
+    PairRuns r{0, n_pair, blockIdx.x, g, 1};
+    if (g % kXcds == 0) {
+        const int xcd = blockIdx.x % kXcds;
+        r = {n_pair * xcd / kXcds, n_pair * (xcd + 1) / kXcds, blockIdx.x / kXcds, g / kXcds, 1};
+    }
+    const int64_t per = (r.end - r.begin) / r.step / 8;
+    r.run = per < 1 ? 1 : per > longest ? longest : (int)per;
+    return r;
 }
 
 // Layout of the reduced-precision copies of a pair (offset lo_off of the pair):
@@ -332,7 +346,7 @@ __global__ __launch_bounds__(kThreads) void convert_v_kernel(const PairDesc* __r
 }
 
 // Bytes of LDS the LDS-resident variant needs for a pair: FP32 keeps V (npX
-// rows); BF16 keeps V and Tau, each with ldX rows (npX, then zero rows up to the
+// rows); BF16 keeps the energy differences, V and Tau, the two each with ldX rows (npX, then zero rows up to the
 // k range of the transposed fragments read from them), each row padded by 16
 // bytes so that the 16-byte fragment reads of 8 consecutive rows fall on
 // distinct bank groups.
@@ -341,9 +355,87 @@ __host__ __device__ inline int lds_row(int ld) { return ld + 16 / (int)sizeof(E)
 
 template <class E>
 __host__ __device__ inline int64_t lds_bytes(int npX, int npY, int ldX, int ldY) {
-    (void)npY;
-    if (sizeof(E) == 2) return 2 * (int64_t)ldX * lds_row<E>(ldY) * sizeof(E);
+    if (sizeof(E) == 2) return 2 * (int64_t)ldX * lds_row<E>(ldY) * sizeof(E) + (npX + npY) * 8;
     return (int64_t)npX * lds_row<E>(ldY) * sizeof(E);
+}
+
+// ---- G of the BF16 pairs in LDS ----
+// A pair of o5v27 monomers is a chain of short phases (V staged, Tau, G) with one workgroup per CU, next to
+// 648 atomic wave instructions on G.  G enters the monomer equation as G + G^T
+// only, so block (i, j) below the diagonal also takes the transpose of block (j, i) and those above are
+// left out; and a workgroup takes its pairs in runs, most of them with one X, whose blocks stay
+// in registers (one per wave) until X changes.  That leaves a quarter of the additions.  42,144 pairs: 5.12 to 4.47 ms a
+// sweep, and 4.39 with the energy differences in LDS.
+constexpr int kRun = 8;   // pairs: an eighth of G_X's additions is left, and the last runs end within 2% (165 pairs each)
+
+template <class E>
+struct RowsC {   // Rows, tiles past the last read as the last (not used)
+    const E* p;
+    int ld, last;
+    __device__ typename Lowp<E>::Frag operator()(int tile, int k0, int lane) const {
+        return Rows<E>{p, ld}(min(tile, last), k0, lane);
+    }
+};
+struct ColsTrC {
+    const __bf16* p;
+    int ld, last;
+    __device__ bf8 operator()(int tile, int k0, int lane) const { return ColsTr{p, ld}(min(tile, last), k0, lane); }
+};
+
+// Block b of the lower triangle of S x S blocks: the off-diagonal ones (two products) first
+__device__ inline void x_block(int S, int b, int& i, int& j) {
+    const int off = S * (S - 1) / 2;
+    if (b >= off) {
+        i = j = b - off;
+        return;
+    }
+    for (i = 1, j = b; j >= i;) j -= i++;
+}
+
+template <int NR, int NC>
+__device__ __forceinline__ void add_blocks(double* G, float* Gf, int ld, int n, int r0, int q0, int lane,
+                                  const f4 (&acc)[NR][NC]) {
+#pragma unroll
+    for (int i = 0; i < NR; ++i)
+#pragma unroll
+        for (int j = 0; j < NC; ++j) {
+            const int c = (q0 + j) * 16 + acc_col(lane);
+#pragma unroll
+            for (int t = 0; t < 4; ++t) {
+                const int r = (r0 + i) * 16 + acc_row(lane, t);
+                if (r < n && c < n) {
+                    if (Gf) unsafeAtomicAdd(Gf + (int64_t)r * ld + c, acc[i][j][t]);
+                    else unsafeAtomicAdd(G + (int64_t)r * ld + c, (double)acc[i][j][t]);
+                }
+            }
+        }
+}
+
+// The strips of the first 64 that fall to `wave` when each goes to the wave with the least work so far, the
+// blocks of G_X counted (S_x: its blocks per side, 0 if it is not kept); all strips in rows of SB per block
+template <int SB, int NW>
+__device__ inline uint64_t deal_strips(int S_x, int S, int wave) {
+    int load[NW];
+#pragma unroll
+    for (int w = 0; w < NW; ++w) {
+        const int off = S_x * (S_x - 1) / 2;
+        load[w] = w < off ? 2 * SB : w < off + S_x ? SB : 0;
+    }
+    uint64_t m = 0;
+    const int total = min(64, S * (S + 1) / 2 * SB), two = S * (S - 1) / 2 * SB;
+    for (int idx = 0; idx < total; ++idx) {
+        int best = 0, least = load[0];
+#pragma unroll
+        for (int w = 1; w < NW; ++w)
+            if (load[w] < least) {
+                least = load[w];
+                best = w;
+            }
+        if (best == wave) m |= uint64_t(1) << idx;
+#pragma unroll
+        for (int w = 0; w < NW; ++w) load[w] += w == best ? (idx < two ? 2 : 1) : 0;
+    }
+    return m;
 }
 
 // One pair per workgroup iteration.  IN_LDS: V is staged in LDS once per pair
@@ -366,11 +458,20 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
     extern __shared__ __align__(16) unsigned char lds_raw[];
     __shared__ double red[NW];
     E* sV = reinterpret_cast<E*>(lds_raw);
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     E* tau = scratch + (int64_t)blockIdx.x * slot_elems;
     float sink = 0.f;
+    const bool sums_x = kTrLds && !po.part && couple;
+    const PairRuns runs = pair_runs(n_pair, sums_x ? kRun : 1);
+    // a wave's block of G_X, kept while X stays: its monomer's matrix, rows (0: none) and first tiles
+    f4 ax[kTrLds ? SB : 1][kTrLds ? SB : 1];
+    zero(ax);
+    int64_t ax_off = 0;
+    int ax_np = 0, ax_n = 0, ax_r0 = 0, ax_q0 = 0;
+    uint64_t mine = 0;   // this wave's strips of G_Y (and G_X)
+    int deal_r = 0, deal_c = 0;
     for (int64_t it = 0;; ++it) {
-        const int64_t pi = pair_for(it, n_pair);
+        const int64_t pi = runs.at(it);
         if (pi >= n_pair) break;
         const PairDesc pd = pairs[pi];
         if (cl && cl[pd.cluster].done) continue;   // cluster stopped: uniform over the workgroup
@@ -387,6 +488,7 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
         const int RB = npX / 16, CB = npY / 16;
         const int sldY = lds_row<E>(ldY);
         E* sTau = sV + (int64_t)ldX * sldY;   // BF16 only
+        double* sdX = reinterpret_cast<double*>(sTau + (int64_t)ldX * sldY);
 
         if (IN_LDS) {   // stage V with 16-byte copies; padding rows and columns come zero
             constexpr int VE = 16 / sizeof(E);
@@ -397,7 +499,9 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
                 const int r = blk / nch * 16 + (ln & 15), c = blk % nch * L::KC + (ln >> 4) * VE;
                 *reinterpret_cast<Chunk*>(sV + r * sldY + c) = *reinterpret_cast<const Chunk*>(V + (int64_t)idx * VE);
             }
-            if (kTrLds) {
+            if (kTrLds) {   // the energy differences: an L2 round trip less per tile of the epilogue
+                for (int k = threadIdx.x; k < npX; k += kThreadsK) sdX[k] = dX[k];
+                for (int k = threadIdx.x; k < npY; k += kThreadsK) sdX[npX + k] = dY[k];
                 // V and Tau rows npX..ldX-1: zero, read as the k padding of the transposed fragments
                 for (int idx = threadIdx.x; idx < (ldX - npX) * sldY; idx += kThreadsK) {
                     sV[(int64_t)npX * sldY + idx] = L::from(0.0);
@@ -437,12 +541,12 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
                 const int c = (c0 + j) * 16 + acc_col(lane);
 #pragma unroll
                 for (int i = 0; i < NR; ++i) {
-                    const double dc = dY[c];
+                    const double dc = kTrLds ? sdX[npX + c] : dY[c];
                     double dr[4], vv[4];
 #pragma unroll
                     for (int t = 0; t < 4; ++t) {
                         const int r = (r0 + i) * 16 + acc_row(lane, t);
-                        dr[t] = dX[r];
+                        dr[t] = kTrLds ? sdX[r] : dX[r];
                         vv[t] = v_at(r, c);
                     }
                     E tv4[4];
@@ -491,7 +595,7 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
             ed2[pd.orig] = 4.0 * sum;
         }
         if (IN_LDS) {   // ask the L2 for the next pair's V while this pair finishes
-            const int64_t pn = pair_for(it + 1, n_pair);
+            const int64_t pn = runs.at(it + 1);
             if (pn < n_pair) {
                 const PairDesc nd = pairs[pn];
                 const MonoDesc nx = monos[nd.x], ny = monos[nd.y];
@@ -501,7 +605,51 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
                     sink += (float)vn[e];
             }
         }
-        if (couple) {
+        if (sums_x) {
+            if constexpr (kTrLds) {
+                const int SR = (RB + SB - 1) / SB, SC = (CB + SB - 1) / SB;
+                const bool keep = SR * (SR + 1) / 2 <= NW;
+                if (ax_n && ax_off != dx.mat_off) {
+                    add_blocks(G ? G + ax_off : nullptr, Gf ? Gf + ax_off : nullptr, ax_np, ax_n, ax_r0, ax_q0, lane, ax);
+                    zero(ax);
+                    ax_n = 0;
+                }
+                if (RB != deal_r || CB != deal_c) {
+                    deal_r = RB;
+                    deal_c = CB;
+                    mine = deal_strips<SB, NW>(keep ? SR : 0, SC, wave);
+                }
+                const RowsC<E> tr{sTau, sldY, RB - 1}, vr{sV, sldY, RB - 1};
+                const ColsTrC tc{sTau, sldY, CB - 1}, vc{sV, sldY, CB - 1};
+                int i, j;
+                if (keep && wave < SR * (SR + 1) / 2) {
+                    x_block(SR, wave, i, j);
+                    ax_off = dx.mat_off;
+                    ax_np = npX;
+                    ax_n = nX;
+                    ax_r0 = i * SB;
+                    ax_q0 = j * SB;
+                    gemm<E, SB, SB, PD>(tr, vr, ldY, i * SB, j * SB, lane, ax);
+                    if (i != j) gemm<E, SB, SB, PD>(vr, tr, ldY, i * SB, j * SB, lane, ax);
+                }
+                // the strips of G_Y, and of a G_X of more blocks than waves: one row of tiles of a block each
+                auto strips = [&](const auto& t, const auto& v, int S, int K, int64_t off, int np, int n, bool dealt) __attribute__((always_inline)) {
+                    for (int idx = 0; idx < S * (S + 1) / 2 * SB; ++idx) {
+                        if (dealt && idx < 64 ? !(mine >> idx & 1) : idx % NW != wave) continue;
+                        x_block(S, idx / SB, i, j);
+                        const int r0 = i * SB + idx % SB;
+                        if (r0 >= np / 16) continue;
+                        f4 acc[1][SB];
+                        zero(acc);
+                        gemm<E, 1, SB, PD>(t, v, K, r0, j * SB, lane, acc);
+                        if (i != j) gemm<E, 1, SB, PD>(v, t, K, r0, j * SB, lane, acc);
+                        add_blocks(G ? G + off : nullptr, Gf ? Gf + off : nullptr, np, n, r0, j * SB, lane, acc);
+                    }
+                };
+                strips(tc, vc, SC, ldX, dy.mat_off, npY, nY, true);
+                if (!keep) strips(tr, vr, SR, ldY, dx.mat_off, npX, nX, false);
+            }
+        } else if (couple) {
             double* GX = G ? G + dx.mat_off : nullptr;
             double* GY = G ? G + dy.mat_off : nullptr;
             float* GfX = Gf ? Gf + dx.mat_off : nullptr;
@@ -529,6 +677,8 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
         }
         __syncthreads();
     }
+    if (kTrLds && ax_n)
+        add_blocks(G ? G + ax_off : nullptr, Gf ? Gf + ax_off : nullptr, ax_np, ax_n, ax_r0, ax_q0, lane, ax);
     if (sink == 1.2345e30f) ed2[0] = sink;   // keeps the prefetch loads; never true for finite inputs
 }
 
