@@ -245,7 +245,7 @@ __device__ inline void for_glb_tasks(const GlbTasks& T, int wave, F&& f) {
     }
 }
 
-// tasks of a pair: Tau blocks SR x SC, G blocks SR^2 + SC^2 (SR = ceil(npX / 48), SC = ceil(npY / 48))
+// tasks of a pair: Tau blocks SR x SC, G blocks at and below the diagonal (SR = ceil(npX / 48), SC = ceil(npY / 48))
 int glb_tau_tasks(int npX, int npY);
 int glb_g_tasks(int npX, int npY);
 void launch_pair_fp64_split(const GlbTasks& tau_tasks, const GlbTasks& g_tasks, int n_chunk_pairs,

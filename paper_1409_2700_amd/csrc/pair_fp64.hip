@@ -1001,13 +1001,100 @@ __global__ __launch_bounds__(kThreadsG, 2) void pair_fp64_glb_kernel(
 // ---------------------------------------------------------------------------
 __device__ inline int sb_count(int tiles) { return (tiles + kSB - 1) / kSB; }
 
+// Operands of the two-launch form.  What bounds it is the matrix pipe (v_mfma_f64_16x16x4, 47 TFLOP/s), once a chunk's
+// loads are in flight while the chunk before it is multiplied.  So the loads take no conditions: rows and columns
+// past the pair's last read the last (their products are masked at the end), and only the last, partial chunk
+// of 16 clamps k, where the other operand (M or Tau) is zero.  120 monomers of
+// o5v27 and o8v56: 6.66 to 5.92 ms a sweep (0.21 TFLOP), with G's blocks above the diagonal left out.
+// N tiles' values for the chunk at k0 into f (four k per lane from k0 + lk).
+template <int N>
+struct GlbM {   // rows of M (fragment order)
+    const double* m;
+    int np, r0, lr, lk;
+    template <bool TAIL>
+    __device__ __forceinline__ void load(int k0, double (&f)[N][4]) const {
+#pragma unroll
+        for (int i = 0; i < N; ++i) split(load4_frag(m, np, (r0 + i) * 16 + lr, k0 + lk), f[i]);
+    }
+};
+
+template <int N>
+struct GlbRows {   // rows of a row-major matrix, k along the row
+    const double* row[N];
+    int n, lk;   // length of a row
+    __device__ __forceinline__ GlbRows(const double* m, int rows, int cols, int ld, int r0, int lane)
+        : n(cols), lk((lane >> 4) * 4) {
+#pragma unroll
+        for (int i = 0; i < N; ++i) row[i] = m + (int64_t)min((r0 + i) * 16 + (lane & 15), rows - 1) * ld;
+    }
+    template <bool TAIL>
+    __device__ __forceinline__ void load(int k0, double (&f)[N][4]) const {
+#pragma unroll
+        for (int i = 0; i < N; ++i)
+#pragma unroll
+            for (int s = 0; s < 4; ++s) f[i][s] = row[i][TAIL ? min(k0 + lk + s, n - 1) : k0 + lk + s];
+    }
+};
+
+template <int N>
+struct GlbCols {   // columns of a row-major matrix, k down the rows
+    const double* m;
+    int n, ld, lk;   // rows
+    int col[N];
+    __device__ __forceinline__ GlbCols(const double* m_, int rows, int cols, int ld_, int c0, int lane)
+        : m(m_), n(rows), ld(ld_), lk((lane >> 4) * 4) {
+#pragma unroll
+        for (int j = 0; j < N; ++j) col[j] = min((c0 + j) * 16 + (lane & 15), cols - 1);
+    }
+    template <bool TAIL>
+    __device__ __forceinline__ void load(int k0, double (&f)[N][4]) const {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const double* q = m + (int64_t)(TAIL ? min(k0 + lk + s, n - 1) : k0 + lk + s) * ld;
+#pragma unroll
+            for (int j = 0; j < N; ++j) f[j][s] = q[col[j]];
+        }
+    }
+};
+
+// acc += A B over k < K
+template <int NR, int NC, class LA, class LB>
+__device__ __forceinline__ void product_glb(const LA& A, const LB& B, int K, d4 (&acc)[NR][NC]) {
+    const int full = K & ~15;
+    double a[NR][4], b[NC][4], an[NR][4], bn[NC][4];
+    if (full) {
+        A.template load<false>(0, an);
+        B.template load<false>(0, bn);
+    }
+    for (int k0 = 0; k0 < full; k0 += 16) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+#pragma unroll
+            for (int i = 0; i < NR; ++i) a[i][s] = an[i][s];
+#pragma unroll
+            for (int j = 0; j < NC; ++j) b[j][s] = bn[j][s];
+        }
+        const int kn = k0 + 16 < full ? k0 + 16 : k0;   // the load past the last chunk repeats it
+        A.template load<false>(kn, an);
+        B.template load<false>(kn, bn);
+        mma_block(acc, a, b);
+    }
+    if (full < K) {
+        A.template load<true>(full, a);
+        B.template load<true>(full, b);
+        mma_block(acc, a, b);
+    }
+}
+
 // Tau = D_XY * (V + M_X V + V M_Y^T) on tiles (r0.., c0..) into the pair's Tau slot; returns the
 // lane's part of <V, Tau>
 template <int NR, int NC>
 __device__ inline double tau_block_glb(const PairView& p, double* tau, int r0, int c0, int lane, int couple) {
     d4 acc[NR][NC];
     zero(acc);
-    tau_sb_glb(p, r0, c0, lane, acc);
+    const int lr = lane & 15, lk = (lane >> 4) * 4;
+    product_glb(GlbM<NR>{p.MX, p.npX, r0, lr, lk}, GlbCols<NC>(p.V, p.nX, p.nY, p.nY, c0, lane), p.nX, acc);   // M_X V
+    product_glb(GlbRows<NR>(p.V, p.nX, p.nY, p.nY, r0, lane), GlbM<NC>{p.MY, p.npY, c0, lr, lk}, p.nY, acc);   // V M_Y^T
     double dxr[NR][4];
 #pragma unroll
     for (int i = 0; i < NR; ++i)
@@ -1047,7 +1134,7 @@ __global__ __launch_bounds__(kThreadsG, 2) void pair_glb_tau_kernel(
     double* __restrict__ scratch, double* __restrict__ ed2, int couple, const Ctrl* __restrict__ ctrl,
     const ClState* __restrict__ cl) {
     if (ctrl && ctrl->done) return;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     for_glb_tasks<kThreadsG / 64>(T, wave, [&](int j, int lt) {
         const PairDesc pd = pairs[T.xpair[j]];
         if (cl && cl[pd.cluster].done) return;   // uniform over the wave
@@ -1068,15 +1155,21 @@ __global__ __launch_bounds__(kThreadsG, 2) void pair_glb_tau_kernel(
     });
 }
 
+// Block (r0, c0) of G_X or G_Y: below the diagonal with the transpose of block (c0, r0) added, since G enters the
+// monomer equation as G + G^T only (half the atomic additions, 206 cycles of the store path per 64 values)
 template <int NR, int NC>
-__device__ inline void g_block_glb(const PairView& p, const double* tau, int which, int r0, int c0, int lane) {
+__device__ inline void g_block_glb(const PairView& p, const double* tau, int which, int r0, int c0, bool both, int lane) {
     d4 acc[NR][NC];
     zero(acc);
     if (which == 0) {
-        gx_sb_glb(p, tau, r0, c0, lane, acc);
+        product_glb(GlbRows<NR>(tau, p.npX, p.npY, p.npY, r0, lane), GlbRows<NC>(p.V, p.nX, p.nY, p.nY, c0, lane), p.nY, acc);
+        if (both)
+            product_glb(GlbRows<NR>(p.V, p.nX, p.nY, p.nY, r0, lane), GlbRows<NC>(tau, p.npX, p.npY, p.npY, c0, lane), p.nY, acc);
         atomic_flush(p.GX, nullptr, p.npX, p.nX, r0, c0, lane, acc);
     } else {
-        gy_sb_glb(p, tau, r0, c0, lane, acc);
+        product_glb(GlbCols<NR>(tau, p.npX, p.npY, p.npY, r0, lane), GlbCols<NC>(p.V, p.nX, p.nY, p.nY, c0, lane), p.nX, acc);
+        if (both)
+            product_glb(GlbCols<NR>(p.V, p.nX, p.nY, p.nY, r0, lane), GlbCols<NC>(tau, p.npX, p.npY, p.npY, c0, lane), p.nX, acc);
         atomic_flush(p.GY, nullptr, p.npY, p.nY, r0, c0, lane, acc);
     }
 }
@@ -1087,22 +1180,23 @@ __global__ __launch_bounds__(kThreadsG, 2) void pair_glb_g_kernel(
     double* __restrict__ G, const double* __restrict__ scratch, const Ctrl* __restrict__ ctrl,
     const ClState* __restrict__ cl) {
     if (ctrl && ctrl->done) return;
-    const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     for_glb_tasks<kThreadsG / 64>(T, wave, [&](int j, int lt) {
         const PairDesc pd = pairs[T.xpair[j]];
         if (cl && cl[pd.cluster].done) return;
         const PairView p = make_view(pd, monos, dif, V, M, G);
         const double* tau = scratch + T.tau_off[j];
         const int RB = p.npX / 16, CB = p.npY / 16, SR = sb_count(RB), SC = sb_count(CB);
-        const int which = lt < SR * SR ? 0 : 1;
-        const int S = which ? SC : SR, n = which ? CB : RB, u = which ? lt - SR * SR : lt;
-        const int r0 = (u / S) * kSB, c0 = (u % S) * kSB;
+        const int nx = SR * (SR + 1) / 2, which = lt < nx ? 0 : 1;
+        int u = which ? lt - nx : lt, i = 0;   // row i of the triangle: blocks (i, 0) .. (i, i)
+        while (u > i) u -= ++i;
+        const int n = which ? CB : RB, r0 = i * kSB, c0 = u * kSB;
         const int nr = min(kSB, n - r0), nc = min(kSB, n - c0);
         if (nr == kSB && nc == kSB) {
-            g_block_glb<kSB, kSB>(p, tau, which, r0, c0, lane);
+            g_block_glb<kSB, kSB>(p, tau, which, r0, c0, r0 != c0, lane);
         } else {
-            for (int i = 0; i < nr; ++i)
-                for (int k = 0; k < nc; ++k) g_block_glb<1, 1>(p, tau, which, r0 + i, c0 + k, lane);
+            for (int e = 0; e < nr; ++e)
+                for (int k = 0; k < nc; ++k) g_block_glb<1, 1>(p, tau, which, r0 + e, c0 + k, r0 != c0, lane);
         }
     });
 }
@@ -1116,7 +1210,7 @@ int glb_tau_tasks(int npX, int npY) {
 
 int glb_g_tasks(int npX, int npY) {
     const int sr = (npX / 16 + kSB - 1) / kSB, sc = (npY / 16 + kSB - 1) / kSB;
-    return sr * sr + sc * sc;
+    return sr * (sr + 1) / 2 + sc * (sc + 1) / 2;
 }
 
 void launch_pair_fp64_split(const GlbTasks& tau_tasks, const GlbTasks& g_tasks, int n_chunk_pairs,
