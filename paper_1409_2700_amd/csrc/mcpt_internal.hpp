@@ -209,10 +209,10 @@ bool pair_fits_lds(int nX, int nY);
 // doubles of a pair's Tau scratch slot: npX npY row-major, or (LDS variant) Tau and its transpose in
 // fragment order over nX and nY rounded up to 8
 int64_t pair_tau_slot(int nX, int nY);
-// Pairs read from L2 in two launches per chunk of at most one pair per persistent workgroup:
-// Tau of every pair (into the chunk's slots of the Tau scratch), then, if couple != 0, G.  Pair k
-// of a chunk belongs to XCD k % 8, whose workgroups take its pairs' tasks (3 x 3 tile blocks) in
-// pair order: a few pairs per XCD at a time, dealt out in even rounds of blocks rather than whole
+// Pairs read from L2 in two launches per chunk:
+// Tau of every pair (into the Tau scratch), then, if couple != 0, G.  The pairs of a chunk are
+// dealt out to the XCDs by their work, whose workgroups take its pairs' tasks (3 x 3 tile blocks) in
+// that order: a few pairs per XCD at a time, dealt out in even rounds of blocks rather than whole
 // pairs per workgroup.  Plain FP64 form only (no dimer source, no stored partials).
 struct GlbTasks {
     const int32_t* xpair;   // processing index of each pair of the chunk, grouped by XCD

@@ -1005,7 +1005,8 @@ __device__ inline int sb_count(int tiles) { return (tiles + kSB - 1) / kSB; }
 // loads are in flight while the chunk before it is multiplied.  So the loads take no conditions: rows and columns
 // past the pair's last read the last (their products are masked at the end), and only the last, partial chunk
 // of 16 clamps k, where the other operand (M or Tau) is zero.  120 monomers of
-// o5v27 and o8v56: 6.66 to 5.92 ms a sweep (0.21 TFLOP), with G's blocks above the diagonal left out.
+// o5v27 and o8v56: 6.66 to 5.92 ms a sweep (0.21 TFLOP), with G's blocks above the diagonal left out, and
+// 5.50 with the pairs dealt to the XCDs by weight.
 // N tiles' values for the chunk at k0 into f (four k per lane from k0 + lk).
 template <int N>
 struct GlbM {   // rows of M (fragment order)

@@ -688,7 +688,8 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
 // times the load path's cycles, and with a few hundred pairs per launch the compute units with one
 // pair more than the others decided its time.  Here a task is a block of up to 4 x 4 tiles of one
 // output, dealt out to the waves of the pair's XCD.  The FP32 pair phase of a batch of 120 monomers of
-// o5v27 and o8v56 (0.21 TFLOP) went from 6.9 to 3.4 ms, 63 TFLOP/s.
+// o5v27 and o8v56 (0.21 TFLOP) went from 6.9 to 3.4 ms; with the pairs dealt to the XCDs by weight it
+// takes 2.93, 73 TFLOP/s.
 constexpr int kThreadsS = 256;   // four waves, two workgroups per CU: 256 registers per lane
 
 // n tiles cut into ceil(n / 4) segments that differ by at most one
