@@ -649,6 +649,8 @@ void record_end(Exec& x, hipEvent_t a, int kind, double flops, double vbytes) {
 #define MCPT_GLB_SPLIT 1
 #endif
 
+constexpr double kFewFlops = 2e6;
+
 // Pairs of a chunk by XCD: the heaviest first (weights: products of a pair), each to the XCD with the least work
 // so far.  Each XCD gets an eighth of some hundred pairs of 0.02 to 0.72 GFLOP, so dealt k % 8 the busiest one
 // decided: 120 monomers of o5v27 and o8v56 took 5.92 ms a sweep in FP64 and 3.39 in FP32, dealt by weight in
@@ -667,12 +669,35 @@ std::array<std::vector<int>, 8> deal_pairs(const std::vector<double>& w) {
     return x;
 }
 
+// Few pairs that fit LDS also run in two launches: a workgroup per pair leaves the other compute units idle.
+// Pair phase in us, two launches against the LDS kernel, by pairs and monomer size n (8 n^3 flops a pair):
+//              n = 27       51         80         100        135
+//   1 pair    17.6 15.8  21.4 26.4  22.3 38.9  23.3 62.7  26.2 104
+//   28        19.4 17.3  22.6 26.9  27.4 40.6  36.8 64.3  59.0 106
+//   55        19.0 14.3  26.6 26.1  34.2 39.3  55.7 64.6  86.5 106
+//   120       21.0 16.8  32.1 28.4  48.5 42.9  87.7 67.9  117  112
+// so at up to a quarter as many pairs as compute units, from 2 MFLOP for the largest on.
+bool few_pairs(const mcpt_ctx* c, const Resident* R) {
+    if (4 * R->n_pair > c->n_cu) return false;
+    double most = 0.0;
+    for (const PairDesc& d : R->pairs) {
+        const double a = R->monos[d.x].n, b = R->monos[d.y].n;
+        most = std::max(most, 4.0 * a * b * (a + b));
+    }
+    return most >= kFewFlops;
+}
+
 // Task layout of the split form for the pairs read from L2 (processing indices n_lds..n_pair):
 // chunks whose Tau fits the Tau scratch (one slot of the largest pair per persistent workgroup: more pairs
 // than workgroups where the sizes differ).
 mcpt_status ensure_glb_plan(mcpt_ctx* c, Resident* R) {
     if (R->glb_plan) return MCPT_OK;
-    const int64_t first = R->n_lds, n = R->n_pair - R->n_lds;
+    const int64_t first = few_pairs(c, R) ? 0 : R->n_lds, n = R->n_pair - first;
+    // one tile per task where 3 x 3 would not give every SIMD one
+    int64_t tasks = 0;
+    for (int64_t k = first; k < R->n_pair && tasks < 4 * c->n_cu; ++k)
+        tasks += glb_tau_tasks(R->monos[R->pairs[k].x].np, R->monos[R->pairs[k].y].np, 3);
+    const int sb = tasks < 4 * c->n_cu ? 1 : 3;
     const int64_t room = (int64_t)std::max(c->grid_glb, 1) * R->max_slot;
     std::vector<int32_t> xpair, pre_tau, pre_g;
     std::vector<int64_t> off;
@@ -705,8 +730,8 @@ mcpt_status ensure_glb_plan(mcpt_ctx* c, Resident* R) {
                 pre_tau.push_back(tt);
                 pre_g.push_back(tg);
                 o += (int64_t)npX * npY;
-                tt += glb_tau_tasks(npX, npY);
-                tg += glb_g_tasks(npX, npY);
+                tt += glb_tau_tasks(npX, npY, sb);
+                tg += glb_g_tasks(npX, npY, sb);
             }
         }
         k0 += m;
@@ -719,20 +744,22 @@ mcpt_status ensure_glb_plan(mcpt_ctx* c, Resident* R) {
     R->glb_g.clear();
     R->glb_n.clear();
     if (n > 0) {
-        int32_t *d_xpair = nullptr, *d_pt = nullptr, *d_pg = nullptr;
+        // one buffer and one copy (offsets, pairs, the two prefixes): a first run of a few pairs would notice four
+        const size_t nx = xpair.size(), npre = pre_tau.size();
+        std::vector<int64_t> all(nx + (nx + 2 * npre + 1) / 2);
+        std::memcpy(all.data(), off.data(), nx * 8);
+        int32_t* w32 = reinterpret_cast<int32_t*>(all.data() + nx);
+        std::memcpy(w32, xpair.data(), nx * 4);
+        std::memcpy(w32 + nx, pre_tau.data(), npre * 4);
+        std::memcpy(w32 + nx + npre, pre_g.data(), npre * 4);
         int64_t* d_off = nullptr;
         mcpt_status st;
-        if ((st = dev_alloc(c, R, &d_xpair, (int64_t)xpair.size())) != MCPT_OK ||
-            (st = dev_alloc(c, R, &d_off, (int64_t)off.size())) != MCPT_OK ||
-            (st = dev_alloc(c, R, &d_pt, (int64_t)pre_tau.size())) != MCPT_OK ||
-            (st = dev_alloc(c, R, &d_pg, (int64_t)pre_g.size())) != MCPT_OK)
-            return st;
-        HIP_TRY(hipMemcpy(d_xpair, xpair.data(), xpair.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(d_off, off.data(), off.size() * sizeof(int64_t), hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(d_pt, pre_tau.data(), pre_tau.size() * sizeof(int32_t), hipMemcpyHostToDevice));
-        HIP_TRY(hipMemcpy(d_pg, pre_g.data(), pre_g.size() * sizeof(int32_t), hipMemcpyHostToDevice));
+        if ((st = dev_alloc(c, R, &d_off, (int64_t)all.size())) != MCPT_OK) return st;
+        HIP_TRY(hipMemcpy(d_off, all.data(), all.size() * 8, hipMemcpyHostToDevice));
+        int32_t* d_xpair = reinterpret_cast<int32_t*>(d_off + nx);
+        int32_t *d_pt = d_xpair + nx, *d_pg = d_pt + npre;
         for (const Bases& b : bases) {
-            GlbTasks t{d_xpair + b.x, d_off + b.x, d_pt + b.p, {}};
+            GlbTasks t{d_xpair + b.x, d_off + b.x, d_pt + b.p, {}, sb};
             for (int i = 0; i < 9; ++i) t.xbeg[i] = b.xbeg[i];
             GlbTasks g = t;
             g.pre = d_pg + b.p;
@@ -781,13 +808,15 @@ void pair_phase(mcpt_ctx* c, Exec& x, Resident* R, double* G, int couple, const 
     }
     const int g_lds = x.grid_cap > 0 ? std::min(c->grid_lds, x.grid_cap) : c->grid_lds;
     const int g_glb = x.grid_cap > 0 ? std::min(c->grid_glb, x.grid_cap) : c->grid_glb;
-    launch_pair_fp64(1, p0, R->d_pairs, R->n_lds, R->d_monos, R->d_dif, R->d_V, R->d_M, G, x.d_scratch,
-                     x.scratch_slot, g_lds, R->d_ed2, couple, ctrl, cl, x.stream);
     // pairs from L2: split into Tau and G launches per chunk (XCD-local tasks) in the plain form
     // (not in deterministic mode, energy pass included: the split form adds E_D2 with atomics)
-    const bool split = MCPT_GLB_SPLIT && R->n_pair > R->n_lds && !R->dimer && !R->det_on && !x.fixed_scratch &&
+    const bool few = few_pairs(c, R);
+    const bool split = MCPT_GLB_SPLIT && (few || R->n_pair > R->n_lds) && !R->dimer && !R->det_on && !x.fixed_scratch &&
                        x.grid_cap == 0 && x.scratch_slots >= c->grid_glb && x.scratch_slot >= R->max_slot &&
                        ensure_glb_plan(c, R) == MCPT_OK;
+    if (!split || !few)
+        launch_pair_fp64(1, p0, R->d_pairs, R->n_lds, R->d_monos, R->d_dif, R->d_V, R->d_M, G, x.d_scratch,
+                         x.scratch_slot, g_lds, R->d_ed2, couple, ctrl, cl, x.stream);
     if (split) {
         for (size_t k = 0; k < R->glb_n.size(); ++k)
             launch_pair_fp64_split(R->glb_tau[k], R->glb_g[k], R->glb_n[k], R->d_pairs, R->d_monos, R->d_dif,
@@ -995,7 +1024,7 @@ void ensure_lo_plan(mcpt_ctx* c, Exec& x, Resident* R, int prec, size_t bytes) {
             return;
     for (const Chunk& b : chunks) {
         GlbTasks t{static_cast<int32_t*>(pv[0]) + b.x, static_cast<int64_t*>(pv[1]) + b.x,
-                   static_cast<int32_t*>(pv[2]) + b.p, {}};
+                   static_cast<int32_t*>(pv[2]) + b.p, {}, 0};
         for (int i = 0; i < 9; ++i) t.xbeg[i] = b.xbeg[i];
         GlbTasks g = t;
         g.pre = static_cast<int32_t*>(pv[3]) + b.p;
@@ -1858,7 +1887,7 @@ mcpt_status run(mcpt_ctx* c, Exec& x, Resident* R, const mcpt_options* o, mcpt_s
     if ((st = ensure_scratch(c, x, R->max_slot)) != MCPT_OK) return st;
     // the split form's task layout, built here because its copies may not run under graph capture
     // (the solve that allocates nothing keeps the one-launch kernel)
-    if (!x.fixed_scratch && (st = ensure_glb_plan(c, R)) != MCPT_OK) return st;
+    if (!x.fixed_scratch && (st = ensure_glb_plan(c, R)) != MCPT_OK && R->n_pair > R->n_lds) return st;
     if (R->dimer && o->precision != MCPT_FP64)
         return fail(MCPT_ERR_INVALID, "a problem with dimer-internal terms runs in FP64 only");
     if (R->lccd && o->deterministic)

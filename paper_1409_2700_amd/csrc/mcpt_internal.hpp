@@ -219,6 +219,7 @@ struct GlbTasks {
     const int64_t* tau_off; // element offset of its Tau in the scratch (row stride npY)
     const int32_t* pre;     // exclusive prefix of the pairs' task counts (n + 1 entries)
     int xbeg[9];            // XCD x's pairs: xpair[xbeg[x] .. xbeg[x + 1])
+    int sb;                 // FP64: edge of a task's block in tiles, 3 or 1
 };
 constexpr int kTaskXcds = 8;
 // the pair j of XCD group [b, e) that task t falls in (pre: exclusive prefix of task counts)
@@ -245,9 +246,9 @@ __device__ inline void for_glb_tasks(const GlbTasks& T, int wave, F&& f) {
     }
 }
 
-// tasks of a pair: Tau blocks SR x SC, G blocks at and below the diagonal (SR = ceil(npX / 48), SC = ceil(npY / 48))
-int glb_tau_tasks(int npX, int npY);
-int glb_g_tasks(int npX, int npY);
+// tasks of a pair: Tau blocks SR x SC, G blocks at and below the diagonal (SR = ceil(npX / (16 sb)), SC likewise)
+int glb_tau_tasks(int npX, int npY, int sb);
+int glb_g_tasks(int npX, int npY, int sb);
 void launch_pair_fp64_split(const GlbTasks& tau_tasks, const GlbTasks& g_tasks, int n_chunk_pairs,
                             const PairDesc* pairs, const MonoDesc* monos, const double* dif, const double* V,
                             const double* M, double* G, double* scratch, int grid, double* ed2, int couple,

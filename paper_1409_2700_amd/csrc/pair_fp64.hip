@@ -1141,9 +1141,9 @@ __global__ __launch_bounds__(kThreadsG, 2) void pair_glb_tau_kernel(
         if (cl && cl[pd.cluster].done) return;   // uniform over the wave
         const PairView p = make_view(pd, monos, dif, V, M, nullptr);
         double* tau = scratch + T.tau_off[j];
-        const int RB = p.npX / 16, CB = p.npY / 16, SC = sb_count(CB);
-        const int r0 = (lt / SC) * kSB, c0 = (lt % SC) * kSB;
-        const int nr = min(kSB, RB - r0), nc = min(kSB, CB - c0);
+        const int RB = p.npX / 16, CB = p.npY / 16, SC = (CB + T.sb - 1) / T.sb;
+        const int r0 = (lt / SC) * T.sb, c0 = (lt % SC) * T.sb;
+        const int nr = min(T.sb, RB - r0), nc = min(T.sb, CB - c0);
         double epart = 0.0;
         if (nr == kSB && nc == kSB) {
             epart = tau_block_glb<kSB, kSB>(p, tau, r0, c0, lane, couple);
@@ -1187,12 +1187,12 @@ __global__ __launch_bounds__(kThreadsG, 2) void pair_glb_g_kernel(
         if (cl && cl[pd.cluster].done) return;
         const PairView p = make_view(pd, monos, dif, V, M, G);
         const double* tau = scratch + T.tau_off[j];
-        const int RB = p.npX / 16, CB = p.npY / 16, SR = sb_count(RB), SC = sb_count(CB);
+        const int RB = p.npX / 16, CB = p.npY / 16, SR = (RB + T.sb - 1) / T.sb;
         const int nx = SR * (SR + 1) / 2, which = lt < nx ? 0 : 1;
         int u = which ? lt - nx : lt, i = 0;   // row i of the triangle: blocks (i, 0) .. (i, i)
         while (u > i) u -= ++i;
-        const int n = which ? CB : RB, r0 = i * kSB, c0 = u * kSB;
-        const int nr = min(kSB, n - r0), nc = min(kSB, n - c0);
+        const int n = which ? CB : RB, r0 = i * T.sb, c0 = u * T.sb;
+        const int nr = min(T.sb, n - r0), nc = min(T.sb, n - c0);
         if (nr == kSB && nc == kSB) {
             g_block_glb<kSB, kSB>(p, tau, which, r0, c0, r0 != c0, lane);
         } else {
@@ -1204,13 +1204,13 @@ __global__ __launch_bounds__(kThreadsG, 2) void pair_glb_g_kernel(
 
 }  // namespace
 
-int glb_tau_tasks(int npX, int npY) {
-    const int sr = (npX / 16 + kSB - 1) / kSB, sc = (npY / 16 + kSB - 1) / kSB;
+int glb_tau_tasks(int npX, int npY, int sb) {
+    const int sr = (npX / 16 + sb - 1) / sb, sc = (npY / 16 + sb - 1) / sb;
     return sr * sc;
 }
 
-int glb_g_tasks(int npX, int npY) {
-    const int sr = (npX / 16 + kSB - 1) / kSB, sc = (npY / 16 + kSB - 1) / kSB;
+int glb_g_tasks(int npX, int npY, int sb) {
+    const int sr = (npX / 16 + sb - 1) / sb, sc = (npY / 16 + sb - 1) / sb;
     return sr * (sr + 1) / 2 + sc * (sc + 1) / 2;
 }
 
