@@ -454,6 +454,7 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
     typedef Lowp<E> L;
     constexpr int kThreadsK = NW * 64;
     constexpr bool kTrLds = IN_LDS && sizeof(E) == 2;
+    constexpr bool kKeep = kTrLds && SB <= 3 && NW <= 8;
     if (ctrl && ctrl->done) return;
     extern __shared__ __align__(16) unsigned char lds_raw[];
     __shared__ double red[NW];
@@ -462,9 +463,9 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
     E* tau = scratch + (int64_t)blockIdx.x * slot_elems;
     float sink = 0.f;
     const bool sums_x = kTrLds && !po.part && couple;
-    const PairRuns runs = pair_runs(n_pair, sums_x ? kRun : 1);
-    // a wave's block of G_X, kept while X stays: its monomer's matrix, rows (0: none) and first tiles
-    f4 ax[kTrLds ? SB : 1][kTrLds ? SB : 1];
+    const PairRuns runs = pair_runs(n_pair, kKeep && sums_x ? kRun : 1);
+    // a wave's block of G_X, kept while X stays (not in the shapes without registers to spare): its monomer's matrix, rows (0: none) and first tiles
+    f4 ax[kKeep ? SB : 1][kKeep ? SB : 1];
     zero(ax);
     int64_t ax_off = 0;
     int ax_np = 0, ax_n = 0, ax_r0 = 0, ax_q0 = 0;
@@ -608,7 +609,7 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
         if (sums_x) {
             if constexpr (kTrLds) {
                 const int SR = (RB + SB - 1) / SB, SC = (CB + SB - 1) / SB;
-                const bool keep = SR * (SR + 1) / 2 <= NW;
+                const bool keep = kKeep && SR * (SR + 1) / 2 <= NW;
                 if (ax_n && ax_off != dx.mat_off) {
                     add_blocks(G ? G + ax_off : nullptr, Gf ? Gf + ax_off : nullptr, ax_np, ax_n, ax_r0, ax_q0, lane, ax);
                     zero(ax);
@@ -622,7 +623,7 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
                 const RowsC<E> tr{sTau, sldY, RB - 1}, vr{sV, sldY, RB - 1};
                 const ColsTrC tc{sTau, sldY, CB - 1}, vc{sV, sldY, CB - 1};
                 int i, j;
-                if (keep && wave < SR * (SR + 1) / 2) {
+                if constexpr (kKeep) if (keep && wave < SR * (SR + 1) / 2) {
                     x_block(SR, wave, i, j);
                     ax_off = dx.mat_off;
                     ax_np = npX;
@@ -677,7 +678,7 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
         }
         __syncthreads();
     }
-    if (kTrLds && ax_n)
+    if (kKeep && ax_n)
         add_blocks(G ? G + ax_off : nullptr, Gf ? Gf + ax_off : nullptr, ax_np, ax_n, ax_r0, ax_q0, lane, ax);
     if (sink == 1.2345e30f) ed2[0] = sink;   // keeps the prefetch loads; never true for finite inputs
 }
