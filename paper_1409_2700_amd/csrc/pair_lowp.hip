@@ -363,10 +363,10 @@ __host__ __device__ inline int64_t lds_bytes(int npX, int npY, int ldX, int ldY)
 // A pair of o5v27 monomers is a chain of short phases (V staged, Tau, G) with one workgroup per CU, next to
 // 648 atomic wave instructions on G.  G enters the monomer equation as G + G^T
 // only, so block (i, j) below the diagonal also takes the transpose of block (j, i) and those above are
-// left out; and a workgroup takes its pairs in runs, most of them with one X, whose blocks stay
-// in registers (one per wave) until X changes.  That leaves a quarter of the additions.  42,144 pairs: 5.12 to 4.47 ms a
-// sweep, and 4.39 with the energy differences in LDS.
-constexpr int kRun = 8;   // pairs: an eighth of G_X's additions is left, and the last runs end within 2% (165 pairs each)
+// left out; and a workgroup takes its pairs in runs, within which X changes seldom, and whose G_X blocks stay
+// in registers (one per wave) until it does.  42,144 pairs: the bytes written go from 6.19 to 2.91 GB and a sweep from 5.12 to
+// 4.47 ms, and to 4.32 with the energy differences in LDS.
+constexpr int kRun = 8;   // pairs: a block row of the pair order, and the last runs end within 2% (165 pairs each)
 
 template <class E>
 struct RowsC {   // Rows, tiles past the last read as the last (not used)
