@@ -52,7 +52,7 @@ void free_lowp(mcpt_ctx* c, Resident* r) {
     r->lo_prec = 0;
     r->d_Vlo = r->d_Mlo = nullptr;
     r->d_lo_off = r->d_mlo_off = nullptr;
-    r->lo_plan = false;
+    r->lo_plan = r->lo_plan_tried = false;
     r->lo_tau.clear();
     r->lo_g.clear();
     r->lo_n.clear();
@@ -678,7 +678,7 @@ std::array<std::vector<int>, 8> deal_pairs(const std::vector<double>& w) {
 //   120       21.0 16.8  32.1 28.4  48.5 42.9  87.7 67.9  117  112
 // so at up to a quarter as many pairs as compute units, from 2 MFLOP for the largest on.
 bool few_pairs(const mcpt_ctx* c, const Resident* R) {
-    if (4 * R->n_pair > c->n_cu) return false;
+    if (R->no_few || 4 * R->n_pair > c->n_cu) return false;
     double most = 0.0;
     for (const PairDesc& d : R->pairs) {
         const double a = R->monos[d.x].n, b = R->monos[d.y].n;
@@ -965,7 +965,8 @@ mcpt_status ensure_lowp(mcpt_ctx* c, Exec& x, Resident* R, int prec) {
 // `bytes` of scratch.  Without memory for them the pairs
 // keep to the one-launch kernel.
 void ensure_lo_plan(mcpt_ctx* c, Exec& x, Resident* R, int prec, size_t bytes) {
-    if (R->lo_plan || R->n_pair == R->lo_n_lds) return;
+    if (R->lo_plan_tried || R->n_pair == R->lo_n_lds) return;
+    R->lo_plan_tried = true;
     const int64_t first = R->lo_n_lds, n = R->n_pair - first, room = (int64_t)(bytes / (prec == MCPT_BF16 ? 2 : 4));
     const int kc = lowp_chunk(prec);
     auto elems = [&](int64_t k) {
@@ -1887,7 +1888,10 @@ mcpt_status run(mcpt_ctx* c, Exec& x, Resident* R, const mcpt_options* o, mcpt_s
     if ((st = ensure_scratch(c, x, R->max_slot)) != MCPT_OK) return st;
     // the split form's task layout, built here because its copies may not run under graph capture
     // (the solve that allocates nothing keeps the one-launch kernel)
-    if (!x.fixed_scratch && (st = ensure_glb_plan(c, R)) != MCPT_OK && R->n_pair > R->n_lds) return st;
+    if (!x.fixed_scratch && (st = ensure_glb_plan(c, R)) != MCPT_OK) {
+        if (R->n_pair > R->n_lds) return st;
+        R->no_few = true;   // all pairs fit LDS: as before, without lists
+    }
     if (R->dimer && o->precision != MCPT_FP64)
         return fail(MCPT_ERR_INVALID, "a problem with dimer-internal terms runs in FP64 only");
     if (R->lccd && o->deterministic)

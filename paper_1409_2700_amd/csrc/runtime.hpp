@@ -68,7 +68,7 @@ struct Resident {
     int64_t lo_slot = 0;          // elements of one low-precision Tau + Tau^T scratch slot
     double lo_v_bytes = 0.0;      // bytes of the low-precision V and V^T
     // its pairs read from L2, chunk by chunk (the Tau of a chunk fits lo_plan_bytes of scratch)
-    bool lo_plan = false;
+    bool lo_plan = false, lo_plan_tried = false;
     size_t lo_plan_bytes = 0;
     std::vector<GlbTasks> lo_tau, lo_g;
     std::vector<int> lo_n;
@@ -129,6 +129,7 @@ struct Resident {
     // pairs read from L2 in the split form (launch_pair_fp64_split): per chunk of at most one pair
     // per persistent workgroup, the XCD-grouped pair lists, Tau offsets and task prefixes
     bool glb_plan = false;
+    bool no_few = false;          // no memory for the task lists of few pairs that fit LDS: one launch
     std::vector<GlbTasks> glb_tau, glb_g;
     std::vector<int> glb_n;
     // served batches with admission at sweep ticks: the G buffer the next sweep accumulates
