@@ -2151,6 +2151,7 @@ mcpt_status run(mcpt_ctx* c, Exec& x, Resident* R, const mcpt_options* o, mcpt_s
         }
         launch_fill(R->d_res, R->n_mono, 0.0, s);   // those sweeps' residuals are nobody's
         fp64_sweep();
+        int issued = 1;   // FP64 sweeps; the device stops at max_sweeps, and so does the host whatever it reads
         if ((st = sync_ctrl(x)) != MCPT_OK) return st;
         if (o->graph && !h.done) {
             // one body = correction + FP64 sweep; bodies per graph chosen so that a replay
@@ -2189,14 +2190,16 @@ mcpt_status run(mcpt_ctx* c, Exec& x, Resident* R, const mcpt_options* o, mcpt_s
                 cur = cur0;
                 cur32 = cur32_0;
             }
-            while (!h.done) {
+            while (!h.done && issued < o->max_sweeps) {
                 HIP_TRY(hipGraphLaunch(R->graph, s));
+                issued += gb;
                 if ((st = sync_ctrl(x)) != MCPT_OK) return st;
             }
         }
-        while (!h.done) {
+        while (!h.done && issued < o->max_sweeps) {
             correction();
             fp64_sweep();
+            ++issued;
             if ((st = sync_ctrl(x)) != MCPT_OK) return st;
         }
         n_hi = h.sweeps;

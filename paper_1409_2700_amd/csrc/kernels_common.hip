@@ -438,12 +438,22 @@ __global__ __launch_bounds__(kReduceThreads) void energy_kernel(const MonoDesc* 
 // Convergence test of one sweep, one workgroup per cluster: max|dT| over the
 // cluster's monomers (cleared for the next sweep), its residual history and the stopping rules (tolerance,
 // divergence, sweep limit).  Clusters that have stopped are left untouched.  One cluster's
-// state is the batch's (reduce_ctrl_kernel has nothing to add: one launch less per sweep).
+// state is the batch's (reduce_ctrl_kernel has nothing to add: one launch less per sweep), also where
+// the cluster was stopped before its first sweep (non-finite input).
 __global__ __launch_bounds__(kReduceThreads) void reduce_sweep_kernel(
     const int64_t* __restrict__ cl_mono, double* __restrict__ res, ClState* __restrict__ cl,
     double* __restrict__ hist_all, Ctrl* __restrict__ ctrl) {
     const int q = blockIdx.x;
-    if (ctrl->done || cl[q].done) return;
+    if (ctrl->done) return;
+    if (cl[q].done) {
+        if (gridDim.x == 1 && threadIdx.x == 0) {
+            ctrl->sweeps = cl[q].sweeps;
+            ctrl->residual = cl[q].residual;
+            ctrl->status = cl[q].status;
+            ctrl->done = 1;
+        }
+        return;
+    }
     __shared__ double sh[kReduceThreads];
     double m = 0.0;
     for (int64_t i = cl_mono[q] + threadIdx.x; i < cl_mono[q + 1]; i += kReduceThreads) {
