@@ -168,10 +168,13 @@ struct Extra {
     int hr, hc;   // 0 or 1
 };
 
-// Nothing but matrix instructions between the fences, and a pause behind them: a v_mfma_f64_4x4x4
-// still reads its operands when the next instructions issue, so a vector instruction that reuses an operand
-// register right behind it would spoil the product (seen where an address was formed in the last fragment's
-// registers), and the compiler keeps no distance there.
+// Nothing but matrix instructions between the fences, then eight wait states, and the operands live until
+// behind those: a v_mfma_f64_4x4x4 still reads its A and B registers when the instructions behind it issue, and a
+// vector instruction that wrote one of them right behind it (an address formed in the last fragment's
+// registers) spoiled the product.  The compiler keeps no distance there and no published table names one, so
+// the eight states are what s_nop takes in one instruction, not a derived bound; the operands of the empty
+// statements keep the register allocator from giving those registers away inside the fences.  The
+// disassembly of the built library is tested for it.
 template <int NR, int NC, int A>
 __device__ __forceinline__ void mma8(double (&acc)[A][A], const double (&a)[NR][2], const double (&b)[NC][2]) {
     __builtin_amdgcn_sched_barrier(0);
@@ -184,6 +187,10 @@ __device__ __forceinline__ void mma8(double (&acc)[A][A], const double (&a)[NR][
                 acc[i][j] = __builtin_amdgcn_mfma_f64_4x4x4f64(a[i][s], b[j][s], acc[i][j], 0, 0, 0);
     __builtin_amdgcn_sched_barrier(0);
     asm volatile("s_nop 7");
+#pragma unroll
+    for (int i = 0; i < NR; ++i) asm volatile("" ::"v"(a[i][0]), "v"(a[i][1]));
+#pragma unroll
+    for (int j = 0; j < NC; ++j) asm volatile("" ::"v"(b[j][0]), "v"(b[j][1]));
     __builtin_amdgcn_sched_barrier(0);
 }
 
