@@ -190,11 +190,14 @@ mcpt_status mcpt_run(mcpt_ctx *ctx, uint64_t id, const mcpt_options *opts, mcpt_
  * capture, tight serving loops, harnesses that forbid hipMalloc): mcpt_run of
  * a resident problem in FP64 (eager sweeps; precision MCPT_FP64, deterministic
  * 0 and graph 0, else MCPT_ERR_INVALID) that allocates nothing.  The Tau
- * scratch of the pair kernels - one slot of the largest pair's padded
- * np_X x np_Y doubles per persistent workgroup - comes from a fixed
- * library-owned device array of MCPT_STATIC_SCRATCH_BYTES instead of the
- * context's allocated scratch; the grid is limited to the slots that fit.  A
- * problem whose largest slot alone exceeds it is rejected (MCPT_ERR_INVALID).
+ * scratch of the pair kernels - per persistent workgroup one slot of the
+ * largest pair's padded np_X x np_Y doubles, or, for pairs whose V block fits in
+ * LDS, of Tau and its transpose (sides padded to 8) - comes from a fixed
+ * library-owned device array instead of the context's allocated scratch.  The
+ * pairs that do not fit in LDS use MCPT_STATIC_SCRATCH_BYTES of it, and their
+ * grid is limited to the slots that fit; the others have a slot for each of 256
+ * compute units (80 MiB in all).  A problem whose largest slot alone exceeds
+ * MCPT_STATIC_SCRATCH_BYTES is rejected (MCPT_ERR_INVALID).
  * Each GPU keeps its own copy of the array until the process ends; every call
  * on one GPU uses that copy, so calls that overlap on a GPU (several contexts
  * or threads) race.  Results, outputs and errors otherwise as mcpt_run (FP64

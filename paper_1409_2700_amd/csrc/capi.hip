@@ -806,7 +806,8 @@ void pair_phase(mcpt_ctx* c, Exec& x, Resident* R, double* G, int couple, const 
             p0.dd = p1.dd = R->d_dd;
         }
     }
-    const int g_lds = x.grid_cap > 0 ? std::min(c->grid_lds, x.grid_cap) : c->grid_lds;
+    const int g_lds = x.grid_cap_lds > 0 ? std::min(c->grid_lds, x.grid_cap_lds) : c->grid_lds;
+    const int64_t slot_lds = x.scratch_slot_lds > 0 ? x.scratch_slot_lds : x.scratch_slot;
     const int g_glb = x.grid_cap > 0 ? std::min(c->grid_glb, x.grid_cap) : c->grid_glb;
     // pairs from L2: split into Tau and G launches per chunk (XCD-local tasks) in the plain form
     // (not in deterministic mode, energy pass included: the split form adds E_D2 with atomics)
@@ -816,7 +817,7 @@ void pair_phase(mcpt_ctx* c, Exec& x, Resident* R, double* G, int couple, const 
                        ensure_glb_plan(c, R) == MCPT_OK;
     if (!split || !few)
         launch_pair_fp64(1, p0, R->d_pairs, R->n_lds, R->d_monos, R->d_dif, R->d_V, R->d_M, G, x.d_scratch,
-                         x.scratch_slot, g_lds, R->d_ed2, couple, ctrl, cl, x.stream);
+                         slot_lds, g_lds, R->d_ed2, couple, ctrl, cl, x.stream);
     if (split) {
         for (size_t k = 0; k < R->glb_n.size(); ++k)
             launch_pair_fp64_split(R->glb_tau[k], R->glb_g[k], R->glb_n[k], R->d_pairs, R->d_monos, R->d_dif,
@@ -2566,14 +2567,20 @@ mcpt_status join_concat(mcpt_ctx* c, Exec& x, const std::vector<std::pair<Reside
 using namespace mcpt;
 
 // Tau scratch of mcpt_run_static, for callers that cannot allocate device memory:
-// one slot of the largest pair's padded npX x npY Tau per persistent workgroup of
-// the FP64 pair kernels.  Each GPU the library runs on holds its own copy for the
+// per persistent workgroup of the FP64 pair kernels one slot of the largest pair
+// (pair_tau_slot).  The two kernels run one after the other, each with slots of its own
+// size from the array's start: the pairs read from L2 have MCPT_STATIC_SCRATCH_BYTES, as the
+// interface says, the pairs in LDS, whose slots hold Tau and its transpose (each smaller
+// than the 20,408 doubles of LDS that V has), all of it, a slot for each of 256
+// compute units.  Each GPU the library runs on holds its own copy for the
 // life of the process.  In host code `scratch` names a host-side stand-in, never
 // the device array: kernels receive the address hipGetSymbolAddress returns for
 // the current device (static_scratch_of).  Every mcpt_run_static on one GPU uses
 // that GPU's copy, so calls that overlap on a GPU race; the pair kernels write
 // each Tau slot in full before reading it, so no clearing is needed.
-static __device__ __align__(256) double scratch[MCPT_STATIC_SCRATCH_BYTES / sizeof(double)];
+constexpr size_t kStaticLdsBytes = size_t(80) << 20;
+static_assert(kStaticLdsBytes >= MCPT_STATIC_SCRATCH_BYTES && kStaticLdsBytes >= 256 * 2 * 20408 * sizeof(double));
+static __device__ __align__(256) double scratch[kStaticLdsBytes / sizeof(double)];
 
 namespace {
 
@@ -2744,6 +2751,12 @@ mcpt_status mcpt_run_static(mcpt_ctx* c, uint64_t id, const mcpt_options* opts, 
     y.scratch_slots = (int)std::min<int64_t>(slots, std::max(c->grid_lds, c->grid_glb));
     y.fixed_scratch = true;
     y.grid_cap = y.scratch_slots;
+    y.scratch_slot_lds = 1;
+    for (int64_t k = 0; k < R->n_lds; ++k) {
+        const PairDesc& d = R->pairs[k];
+        y.scratch_slot_lds = std::max(y.scratch_slot_lds, pair_tau_slot(R->monos[d.x].n, R->monos[d.y].n));
+    }
+    y.grid_cap_lds = (int)std::min<int64_t>(kStaticLdsBytes / sizeof(double) / y.scratch_slot_lds, c->grid_lds);
     try {
         return run(c, y, R, opts, out);
     } catch (const std::exception& e) {

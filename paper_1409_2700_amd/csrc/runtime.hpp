@@ -165,7 +165,8 @@ struct Exec {
     int64_t scratch_slot = 0;
     int scratch_slots = 0;
     bool fixed_scratch = false;         // d_scratch is the library's static array: never reallocated
-    int grid_cap = 0;                   // > 0: FP64 pair-kernel grids limited to the slots that fit
+    int grid_cap = 0, grid_cap_lds = 0; // > 0: FP64 pair-kernel grids (L2, LDS variant) limited to the slots that fit
+    int64_t scratch_slot_lds = 0;       // > 0: doubles per slot of the LDS variant, if not scratch_slot
     void* d_scratch_lo = nullptr;       // reduced-precision Tau and Tau^T
     size_t scratch_lo_bytes = 0;
     double* h_out = nullptr;            // pinned staging of large results (copy_out), made on first need
