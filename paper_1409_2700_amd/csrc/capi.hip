@@ -690,8 +690,12 @@ bool few_pairs(const mcpt_ctx* c, const Resident* R) {
 // Task layout of the split form for the pairs read from L2 (processing indices n_lds..n_pair):
 // chunks whose Tau fits the Tau scratch (one slot of the largest pair per persistent workgroup: more pairs
 // than workgroups where the sizes differ).
-mcpt_status ensure_glb_plan(mcpt_ctx* c, Resident* R) {
+// Made once; where there was no memory for them only a new solve (`again`) tries once more, not every sweep
+// of a served batch, which runs without them.
+mcpt_status ensure_glb_plan(mcpt_ctx* c, Resident* R, bool again = false) {
     if (R->glb_plan) return MCPT_OK;
+    if (R->glb_plan_tried && !again) return MCPT_ERR_NOMEM;
+    R->glb_plan_tried = true;
     const int64_t first = few_pairs(c, R) ? 0 : R->n_lds, n = R->n_pair - first;
     // one tile per task where 3 x 3 would not give every SIMD one
     int64_t tasks = 0;
@@ -1889,7 +1893,7 @@ mcpt_status run(mcpt_ctx* c, Exec& x, Resident* R, const mcpt_options* o, mcpt_s
     if ((st = ensure_scratch(c, x, R->max_slot)) != MCPT_OK) return st;
     // the split form's task layout, built here because its copies may not run under graph capture
     // (the solve that allocates nothing keeps the one-launch kernel)
-    if (!x.fixed_scratch && (st = ensure_glb_plan(c, R)) != MCPT_OK) {
+    if (!x.fixed_scratch && (st = ensure_glb_plan(c, R, true)) != MCPT_OK) {
         if (R->n_pair > R->n_lds) return st;
         R->no_few = true;   // all pairs fit LDS: as before, without lists
     }

@@ -126,9 +126,9 @@ struct Resident {
     // served batches: owned by the scheduler, never visible to the caller under this id
     bool internal = false;
     int refs = 0;                 // tickets still holding this batch's results, + 1 while a worker runs it
-    // pairs read from L2 in the split form (launch_pair_fp64_split): per chunk of at most one pair
-    // per persistent workgroup, the XCD-grouped pair lists, Tau offsets and task prefixes
-    bool glb_plan = false;
+    // pairs read from L2, or few pairs, in the split form (launch_pair_fp64_split): per chunk of pairs whose Tau
+    // fits the Tau scratch, the XCD-grouped pair lists, Tau offsets and task prefixes
+    bool glb_plan = false, glb_plan_tried = false;
     bool no_few = false;          // no memory for the task lists of few pairs that fit LDS: one launch
     std::vector<GlbTasks> glb_tau, glb_g;
     std::vector<int> glb_n;
