@@ -527,13 +527,20 @@ void release_resident(mcpt_ctx* c, uint64_t id) {
 // into the first touch of its pages, one thread of the runtime behind the other with the transfer: 36 ms for
 // the 146 MB of T of 1000 o5v27 monomers, 9 ms this way.  Here each of a few threads takes a part of the array through two
 // pinned chunks of its own, the next transfer in flight while it copies.  Smaller arrays
-// (below kOutMin), and all if there is no staging memory or no thread, go the direct way.
+// (below kOutMin), memory that HIP knows (pinned, or a device's, which the host may not write), and all if
+// there is no staging memory or no thread, go the direct way.
 constexpr int kOutThreads = 8;
 constexpr size_t kOutChunk = size_t(1) << 21;     // bytes; two per thread
 constexpr size_t kOutMin = size_t(1) << 22;
 
 hipError_t copy_out(mcpt_ctx* c, Exec& x, double* dst, const double* src, size_t bytes) {
     hipStream_t s = x.stream;
+    if (bytes >= kOutMin) {
+        hipPointerAttribute_t at;
+        const bool known = hipPointerGetAttributes(&at, dst) == hipSuccess && at.type != hipMemoryTypeUnregistered;
+        (void)hipGetLastError();   // an unknown pointer may be an error there
+        if (known) return hipMemcpyAsync(dst, src, bytes, hipMemcpyDeviceToHost, s);
+    }
     if (bytes >= kOutMin && !x.h_out &&
         hipHostMalloc(reinterpret_cast<void**>(&x.h_out), 2 * kOutThreads * kOutChunk, hipHostMallocDefault) != hipSuccess) {
         (void)hipGetLastError();
