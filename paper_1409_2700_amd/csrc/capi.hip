@@ -1087,8 +1087,9 @@ void lowp_phase(mcpt_ctx* c, Exec& x, Resident* R, double* G, float* Gf, int sou
                      R->d_lo_off, R->d_Mlo, R->d_mlo_off, G, Gf, x.d_scratch_lo, R->lo_slot, x.grid_lo_lds, R->d_ed2,
                      source, 1, nullptr, cl, x.stream);
     // pairs read from L2: two launches per chunk.  Not with stored partials, which the one-launch kernel writes
-    // and whose E_D2 repeats bitwise (the split form adds it with atomics).
-    if (R->lo_plan && !det && x.scratch_lo_bytes >= R->lo_plan_bytes) {
+    // and whose E_D2 repeats bitwise (the split form adds it with atomics); nor in the tuner if no pair is
+    // in LDS: the two launches have one shape, and only the one-launch kernel's can be ranked.
+    if (R->lo_plan && !det && !(every && nl == 0) && x.scratch_lo_bytes >= R->lo_plan_bytes) {
         const int grid = std::max(8, 2 * c->n_cu / 8 * 8);
         for (size_t k = 0; k < R->lo_n.size(); ++k)
             launch_pair_lowp_split(R->lo_prec, R->lo_tau[k], R->lo_g[k], R->lo_n[k], R->d_pairs, R->d_monos, R->d_dif,
