@@ -752,26 +752,32 @@ __device__ __forceinline__ void pair_body_lds(const PairDesc* __restrict__ pairs
         const int RB = p.nx8 / 8, CB = p.ny8 / 8;
         double* sD = sV + p.nx8 * p.ldv;
         double* tauT = tau + (int64_t)p.nx8 * p.ny8;   // Tau (rows of X) and Tau^T in fragment order
-        {   // stage V, zero-padded to nx8 rows of ldv; loads batched
-            constexpr int kRows = 9, kCols = 3;
-            for (int rb = wave; rb < p.nx8; rb += NW * kRows)
-                for (int cb = 0; cb < p.ldv; cb += 64 * kCols) {
-                    double tmp[kRows][kCols];
+        {   // Stage V, zero-padded to nx8 rows of ldv; loads batched, nine rows per wave of three times 64 columns, or
+            // three of one for rows of at most 64, where most of those would be empty: 2,372 pairs of n = 16 took
+            // 80 us a launch with 9 x 3 throughout, 73 with 9 x 1 and take 64; of n = 51, 195, 188 and 185.
+            auto stage = [&](auto cols) __attribute__((always_inline)) {
+                constexpr int kCols = decltype(cols)::N, kRows = kCols == 1 ? 3 : 9;
+                for (int rb = wave; rb < p.nx8; rb += NW * kRows)
+                    for (int cb = 0; cb < p.ldv; cb += 64 * kCols) {
+                        double tmp[kRows][kCols];
 #pragma unroll
-                    for (int k = 0; k < kRows; ++k)
+                        for (int k = 0; k < kRows; ++k)
 #pragma unroll
-                        for (int m = 0; m < kCols; ++m) {
-                            const int r = rb + NW * k, c = cb + lane + 64 * m;
-                            tmp[k][m] = (r < p.nX && c < p.nY) ? p.V[(int64_t)r * p.nY + c] : 0.0;
-                        }
+                            for (int m = 0; m < kCols; ++m) {
+                                const int r = rb + NW * k, c = cb + lane + 64 * m;
+                                tmp[k][m] = (r < p.nX && c < p.nY) ? p.V[(int64_t)r * p.nY + c] : 0.0;
+                            }
 #pragma unroll
-                    for (int k = 0; k < kRows; ++k)
+                        for (int k = 0; k < kRows; ++k)
 #pragma unroll
-                        for (int m = 0; m < kCols; ++m) {
-                            const int r = rb + NW * k, c = cb + lane + 64 * m;
-                            if (r < p.nx8 && c < p.ldv) sV[r * p.ldv + c] = tmp[k][m];
-                        }
-                }
+                            for (int m = 0; m < kCols; ++m) {
+                                const int r = rb + NW * k, c = cb + lane + 64 * m;
+                                if (r < p.nx8 && c < p.ldv) sV[r * p.ldv + c] = tmp[k][m];
+                            }
+                    }
+            };
+            if (p.ldv <= 64) stage(Seg8<1, 0>{});
+            else stage(Seg8<3, 0>{});
             // the energy differences of X's rows and Y's columns (zero in the padding) for the epilogue
             for (int k = threadIdx.x; k < p.nx8 + p.ny8; k += NT) sD[k] = k < p.nx8 ? p.dX[k] : p.dY[k - p.nx8];
             if (threadIdx.x < kEnergySlots) red[threadIdx.x] = 0.0;
