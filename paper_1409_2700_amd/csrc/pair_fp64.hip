@@ -286,10 +286,14 @@ __device__ __forceinline__ Cut cut(int B, int s) {
 }
 
 // Segments of 4 or 5 blocks (17 blocks, n = 135: 5+4+4+4), 2 or 3, or single ones: the longest that R and C can
-// be cut into, and shorter ones when there are too few blocks for eight waves.
+// be cut into, and not 4 or 5 where that leaves too few tasks for eight waves.  2,372 pairs, us a launch with the
+// line at 20, 40 and 64 blocks (Tau: R C, G: R^2 + C^2): n = 32 (16 and 32 blocks) 108, 103, 103; n = 40 (25 and
+// 50) 166, 133, 123; n = 64 (64 and 128) 218 below each, 242 with Tau in shorter ones; n = 72 (81 and 162) 282,
+// and 310.  Single blocks in place of 2 or 3 gain nothing at n = 16 and lose from n = 27 on (103, 125).
+// Sides of 6, 7 and 11 blocks cannot be cut into 4 and 5.
 __device__ __forceinline__ int seg_len(int R, int C, int blocks) {
     auto cuts = [](int B, int s) { return B >= s * ((B + s) / (s + 1)); };
-    if (blocks >= 96 && cuts(R, 4) && cuts(C, 4)) return 4;
+    if (blocks >= 64 && cuts(R, 4) && cuts(C, 4)) return 4;
     return R >= 2 && C >= 2 ? 2 : 1;
 }
 
