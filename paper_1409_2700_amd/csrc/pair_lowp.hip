@@ -289,27 +289,36 @@ __device__ inline double wave_sum(double x) {
     return x;
 }
 
-// The pairs of a workgroup: its XCD's share of the list in runs of `run` pairs, dealt round-robin
+// The pairs of a workgroup: its XCD's share of the list in runs of `run` pairs, dealt round-robin.  Stepped, not
+// computed from a count: the two 64-bit divisions of that, twice a pair, were a twelfth of a small pair's time.
 struct PairRuns {
-    int64_t begin, end, first, step;
-    int run;
-    __device__ int64_t at(int64_t it) const {   // INT64_MAX past the last
-        const int64_t p = begin + (first + it / run * step) * run + it % run;
-        return p < end ? p : INT64_MAX;
+    int64_t p, end, skip;   // the pair, the end of the share, from the last pair of a run to the first of the next
+    int run, left;          // pairs of this run behind p
+    __device__ int64_t at() const { return p < end ? p : INT64_MAX; }
+    __device__ int64_t next() const {
+        const int64_t q = left ? p + 1 : p + skip;
+        return q < end ? q : INT64_MAX;
+    }
+    __device__ void step() {
+        p += left ? 1 : skip;
+        left = left ? left - 1 : run - 1;
     }
 };
 
 // longest > 1: runs of up to that many pairs, at least eight runs per workgroup
 __device__ inline PairRuns pair_runs(int64_t n_pair, int longest) {
-    const int g = gridDim.x;
-    PairRuns r{0, n_pair, blockIdx.x, g, 1};
-    if (g % kXcds == 0) {
+    int64_t begin = 0, end = n_pair;
+    int first = blockIdx.x, step = gridDim.x;
+    if (gridDim.x % kXcds == 0) {
         const int xcd = blockIdx.x % kXcds;
-        r = {n_pair * xcd / kXcds, n_pair * (xcd + 1) / kXcds, blockIdx.x / kXcds, g / kXcds, 1};
+        begin = n_pair * xcd / kXcds;
+        end = n_pair * (xcd + 1) / kXcds;
+        first = blockIdx.x / kXcds;
+        step = gridDim.x / kXcds;
     }
-    const int64_t per = (r.end - r.begin) / r.step / 8;
-    r.run = per < 1 ? 1 : per > longest ? longest : (int)per;
-    return r;
+    const int64_t per = (end - begin) / step / 8;
+    const int run = per < 1 ? 1 : per > longest ? longest : (int)per;
+    return {begin + (int64_t)first * run, end, (int64_t)(step - 1) * run + 1, run, run - 1};
 }
 
 // Layout of the reduced-precision copies of a pair (offset lo_off of the pair):
@@ -463,7 +472,7 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
     E* tau = scratch + (int64_t)blockIdx.x * slot_elems;
     float sink = 0.f;
     const bool sums_x = kTrLds && !po.part && couple;
-    const PairRuns runs = pair_runs(n_pair, kKeep && sums_x ? kRun : 1);
+    PairRuns runs = pair_runs(n_pair, kKeep && sums_x ? kRun : 1);
     // a wave's block of G_X, kept while X stays (not in the shapes without registers to spare): its monomer's matrix, rows (0: none) and first tiles
     f4 ax[kKeep ? SB : 1][kKeep ? SB : 1];
     zero(ax);
@@ -471,8 +480,8 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
     int ax_np = 0, ax_n = 0, ax_r0 = 0, ax_q0 = 0;
     uint64_t mine = 0;   // this wave's strips of G_Y (and G_X)
     int deal_r = 0, deal_c = 0;
-    for (int64_t it = 0;; ++it) {
-        const int64_t pi = runs.at(it);
+    for (;; runs.step()) {
+        const int64_t pi = runs.at();
         if (pi >= n_pair) break;
         const PairDesc pd = pairs[pi];
         if (cl && cl[pd.cluster].done) continue;   // cluster stopped: uniform over the workgroup
@@ -596,7 +605,7 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
             ed2[pd.orig] = 4.0 * sum;
         }
         if (IN_LDS) {   // ask the L2 for the next pair's V while this pair finishes
-            const int64_t pn = runs.at(it + 1);
+            const int64_t pn = runs.next();
             if (pn < n_pair) {
                 const PairDesc nd = pairs[pn];
                 const MonoDesc nx = monos[nd.x], ny = monos[nd.y];
