@@ -471,7 +471,9 @@ __global__ __launch_bounds__(NW * 64) void pair_lowp_kernel(
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
     E* tau = scratch + (int64_t)blockIdx.x * slot_elems;
     float sink = 0.f;
-    const bool sums_x = kTrLds && !po.part && couple;
+    // Lower triangle of G: with few pairs its half as many and twice as long tasks leave waves idle (28 pairs of n = 51:
+    // 15.2 us with all of G, 19.4 with half; 185 of n = 135: 46.6 and 41).
+    const bool sums_x = kTrLds && !po.part && couple && 4 * n_pair > (int64_t)gridDim.x;
     PairRuns runs = pair_runs(n_pair, kKeep && sums_x ? kRun : 1);
     // a wave's block of G_X, kept while X stays (not in the shapes without registers to spare): its monomer's matrix, rows (0: none) and first tiles
     f4 ax[kKeep ? SB : 1][kKeep ? SB : 1];
