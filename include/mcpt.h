@@ -429,8 +429,8 @@ mcpt_status mcpt_fd_stencil(mcpt_ctx *ctx, uint64_t base, int32_t n_modes, const
 /* ---- Device characterization (roofline reporting; not part of the method) ----
  * Sustained FP64 rates of the device, measured with register-only streams of
  * independent operations at two waves per SIMD (the FP64 pair kernel's
- * occupancy): v_mfma_f64_16x16x4 alone, and v_fma_f64 alone, in algorithmic
- * TFLOP/s; the shader clock from the core clock counter against the 100 MHz
+ * occupancy): v_mfma_f64_16x16x4 alone, v_fma_f64 alone, and v_mfma_f64_4x4x4
+ * alone (the instruction of the pairs whose V fits in LDS), in algorithmic TFLOP/s; the shader clock from the core clock counter against the 100 MHz
  * real-time counter (of the last stream).  Allocates and frees its own small
  * buffers on the device; takes ~0.1 s.
  * Errors: MCPT_ERR_INVALID (no such device, NULL), MCPT_ERR_NOMEM, MCPT_ERR_DEVICE. */
@@ -439,6 +439,7 @@ typedef struct {
     double  valu_f64_tflops;
     double  clock_ghz;
     int32_t compute_units;
+    float   mfma_f64_4x4x4_tflops;
 } mcpt_rates;
 mcpt_status mcpt_device_rates(int device, mcpt_rates *out);
 

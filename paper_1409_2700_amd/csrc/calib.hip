@@ -1,5 +1,5 @@
 // Device characterization for roofline reporting (not part of the method): the
-// sustained rates of the two FP64 pipes the pair kernels can use, measured
+// sustained rates of the FP64 instructions the pair kernels use or could use, measured
 // with register-only streams of independent operations at two waves per SIMD
 // (the occupancy of the FP64 pair kernel), and the shader clock read from the
 // core clock counter against the fixed-frequency real-time counter.
@@ -16,9 +16,9 @@ typedef double d4 __attribute__((ext_vector_type(4)));
 
 constexpr int kCalThreads = 256;
 constexpr int kCalAcc = 8;      // independent MFMA accumulators per wave
-constexpr int kCalChains = 16;  // independent FMA chains per lane
+constexpr int kCalChains = 16;  // independent FMA (or 4x4x4 MFMA) chains per lane
 
-// mode 0: v_mfma_f64_16x16x4 only; mode 1: v_fma_f64 only.  out[block * threads + lane]
+// mode 0: v_mfma_f64_16x16x4 only; mode 1: v_fma_f64 only; mode 2: v_mfma_f64_4x4x4 only.  out[block * threads + lane]
 // keeps the results live; clk[2 block] = core-clock cycles, clk[2 block + 1] =
 // real-time (100 MHz) ticks of the block's first wave.
 template <int MODE>
@@ -36,6 +36,11 @@ __global__ __launch_bounds__(kCalThreads) void rate_kernel(double* out, unsigned
         if (MODE == 0) {
 #pragma unroll
             for (int i = 0; i < kCalAcc; ++i) acc[i] = __builtin_amdgcn_mfma_f64_16x16x4f64(a, s, acc[i], 0, 0, 0);
+        } else if (MODE == 2) {
+#pragma unroll
+            for (int r = 0; r < 2; ++r)
+#pragma unroll
+                for (int i = 0; i < kCalChains; ++i) v[i] = __builtin_amdgcn_mfma_f64_4x4x4f64(a, s, v[i], 0, 0, 0);
         } else {
 #pragma unroll
             for (int r = 0; r < 4; ++r)
@@ -76,20 +81,19 @@ extern "C" mcpt_status mcpt_device_rates(int device, mcpt_rates* out) {
     unsigned long long* c = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     mcpt_status st = MCPT_OK;
-    float ms[2] = {0.f, 0.f};
+    float ms[3] = {0.f, 0.f, 0.f};
     unsigned long long h[2] = {0, 0};
     if (hipMalloc(&d, (size_t)blocks * kCalThreads * sizeof(double)) != hipSuccess ||
         hipMalloc(&c, (size_t)2 * blocks * sizeof(unsigned long long)) != hipSuccess ||
         hipEventCreate(&e0) != hipSuccess || hipEventCreate(&e1) != hipSuccess) {
         st = fail(MCPT_ERR_NOMEM, "calibration buffers");
     }
-    for (int mode = 0; mode < 2 && st == MCPT_OK; ++mode) {
+    for (int mode : {0, 2, 1}) {   // the clock is that of the last stream
+        if (st != MCPT_OK) break;
         for (int rep = 0; rep < 2; ++rep) {   // the first launch warms the clocks up, the second is timed
             if (rep == 1) (void)hipEventRecord(e0, nullptr);
-            if (mode == 0)
-                hipLaunchKernelGGL(rate_kernel<0>, dim3(blocks), dim3(kCalThreads), 0, nullptr, d, c, iters, 1.0000001);
-            else
-                hipLaunchKernelGGL(rate_kernel<1>, dim3(blocks), dim3(kCalThreads), 0, nullptr, d, c, iters, 1.0000001);
+            const auto k = mode == 0 ? rate_kernel<0> : mode == 1 ? rate_kernel<1> : rate_kernel<2>;
+            hipLaunchKernelGGL(k, dim3(blocks), dim3(kCalThreads), 0, nullptr, d, c, iters, 1.0000001);
         }
         (void)hipEventRecord(e1, nullptr);
         if (hipEventSynchronize(e1) != hipSuccess || hipEventElapsedTime(&ms[mode], e0, e1) != hipSuccess ||
@@ -100,6 +104,7 @@ extern "C" mcpt_status mcpt_device_rates(int device, mcpt_rates* out) {
         const double waves = (double)blocks * (kCalThreads / 64);
         out->mfma_f64_tflops = waves * iters * kCalAcc * 2048.0 / (ms[0] * 1e-3) / 1e12;
         out->valu_f64_tflops = waves * iters * 4 * kCalChains * 64 * 2.0 / (ms[1] * 1e-3) / 1e12;
+        out->mfma_f64_4x4x4_tflops = (float)(waves * iters * 2 * kCalChains * 512.0 / (ms[2] * 1e-3) / 1e12);
         out->clock_ghz = h[1] ? (double)h[0] / ((double)h[1] / 100e6) / 1e9 : 0.0;
         out->compute_units = prop.multiProcessorCount;
     }

@@ -93,14 +93,14 @@ class mcpt_timing(C.Structure):
 
 class mcpt_rates(C.Structure):
     _fields_ = [("mfma_f64_tflops", C.c_double), ("valu_f64_tflops", C.c_double), ("clock_ghz", C.c_double),
-                ("compute_units", C.c_int32)]
+                ("compute_units", C.c_int32), ("mfma_f64_4x4x4_tflops", C.c_float)]
 
     def as_dict(self) -> dict:
         return {name: getattr(self, name) for name, _ in self._fields_}
 
 
 def device_rates(device: int = 0) -> dict:
-    """mcpt_device_rates: sustained FP64 MFMA and VALU rates and the shader clock."""
+    """mcpt_device_rates: sustained FP64 MFMA (both shapes) and VALU rates and the shader clock."""
     r = mcpt_rates()
     _check(lib().mcpt_device_rates(device, C.byref(r)))
     return r.as_dict()
