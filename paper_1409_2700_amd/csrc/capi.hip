@@ -679,10 +679,10 @@ std::array<std::vector<int>, 8> deal_pairs(const std::vector<double>& w) {
 // Few pairs that fit LDS also run in two launches: a workgroup per pair leaves the other compute units idle.
 // Pair phase in us, two launches against the LDS kernel, by pairs and monomer size n (8 n^3 flops a pair):
 //              n = 27       51         80         100        135
-//   1 pair    17.6 15.8  21.4 26.4  22.3 38.9  23.3 62.7  26.2 104
-//   28        19.4 17.3  22.6 26.9  27.4 40.6  36.8 64.3  59.0 106
-//   55        19.0 14.3  26.6 26.1  34.2 39.3  55.7 64.6  86.5 106
-//   120       21.0 16.8  32.1 28.4  48.5 42.9  87.7 67.9  117  112
+//   1 pair    17.6 14.3  21.4 23.6  22.3 38.9  23.3 62.7  26.2 104
+//   28        19.4 14.4  22.6 23.7  27.4 40.6  36.8 64.3  59.0 106
+//   55        19.0 14.5  26.6 23.9  34.2 39.3  55.7 64.6  86.5 106
+//   120       21.0 14.8  32.1 25.3  48.5 42.9  87.7 67.9  117  112
 // so at up to a quarter as many pairs as compute units, from 2 MFLOP for the largest on.
 bool few_pairs(const mcpt_ctx* c, const Resident* R) {
     if (R->no_few || 4 * R->n_pair > c->n_cu) return false;

@@ -646,7 +646,7 @@ void monomer_dispatch(int max_o, int max_v, int mode, const MonoDesc* monos, int
                       const int64_t* mlo_off, int chunk, double* em2, double* em2_0, double* res, const Ctrl* ctrl,
                       const ClState* cl, hipStream_t s, const double* Lt = nullptr) {
     if (n_mono <= 0) return;
-    // Workgroups per monomer: about four per compute unit of the chip in all, at most one per block pair of
+    // Workgroups per monomer: about sixteen per compute unit of the chip in all, at most one per block pair of
     // the largest monomer (15 for o = 5; a workgroup without one ends at once).  Measured with o5v27: see the kernel.
     const int pairs = max_o * (max_o + 1) / 2;
     const int splits = mode == kMonoE0 ? 1 : std::max(1, std::min(pairs, kMonoGroups / n_mono));

@@ -723,10 +723,11 @@ __device__ inline void pair_body_glb(const PairDesc* __restrict__ pairs, int64_t
 // V resident in LDS (the pair list given to it holds only pairs that fit).
 //
 // What bounds it: the FP64 matrix pipe, and what does not overlap with it.  v_mfma_f64_16x16x4 sustains
-// 47 TFLOP/s on this device, v_mfma_f64_4x4x4 72, and its blocks pad n = 135 to 136 instead of 144.
+// 47 TFLOP/s on this device, v_mfma_f64_4x4x4 76 (both as mcpt_device_rates streams them), and its blocks pad n = 135
+// to 136 instead of 144.
 // On the 1000-monomer crystal the mean of four coupled launches and the energy pass is 16.2 ms (46.0 TFLOP/s;
 // 19.9 ms with 16 x 16 x 4 tiles).  Of the 258,000 cycles of a coupled pair (n = 135) the products take 180,000 (157,000 at the
-// pipe's rate), staging V 14,000, the stores of Tau and Tau^T 27,000 and the atomics behind the last products most of
+// pipe's 16 cycles each), staging V 14,000, the stores of Tau and Tau^T 27,000 and the atomics behind the last products most of
 // the rest: a store or an atomic instruction occupies a CU's memory path for 90 to 200 cycles, whatever its width.
 // ldv = ny8 + 4 puts 8 consecutive rows on distinct 8-bank groups (row reads) and the 4 row pairs of a column read on
 // distinct 16-bank groups.  Tried: tasks of (4-5) x (8-9) blocks, one per wave (17.3 ms: all waves store at
